@@ -4,15 +4,30 @@
 // Parameters are one flat float array: W1[64][16], b1[64], W2[64][64], b2[64],
 // W3[3][64], b3[3] (5443 floats, staged in LDS by every workgroup).
 //
+// A workgroup (four waves) takes tiles of 16 samples; wave w owns the 16 hidden
+// units 16w..16w+15 of both layers.  The layers are matrix products with 16
+// samples as columns, on the FP32 matrix instruction 16x16x4 (FP32 products
+// and sums): a lane holds its unit's weights in registers as the A operand,
+// the B operand is the input row or the LDS tile of the previous layer.  One
+// thread per sample, as before, ran the 10,000 multiply-adds of a sample as
+// one chain on n/64 waves: 4 workgroups for a training batch.
+//
 // Training step = three launches:
-//   k_mlp_samples : one thread per sample: forward pass, softmax, the
-//                   per-sample back-propagated errors of the three layers and
-//                   the sample's loss, written to the workspace;
-//   k_mlp_grad    : the batch sum of every parameter's gradient, 16
-//                   interleaved batch segments per parameter combined in a
-//                   fixed order (deterministic, accumulated in double);
+//   k_mlp_samples : forward pass, softmax, the per-sample back-propagated
+//                   errors of the three layers and the sample's loss, written
+//                   to the workspace;
+//   k_mlp_grad    : the batch sum of every parameter's gradient: a workgroup
+//                   per 16 x 16 tile of a weight matrix, on the FP64 matrix
+//                   instruction (products of floats are exact in it), waves
+//                   over interleaved samples combined in a fixed order
+//                   (deterministic);
 //   k_adam        : element-wise Adam update.
+// Measured on an MI355X at 1024 samples: k_mlp_samples 6.4 us (63 before),
+// k_mlp_grad 11 (38, a thread per parameter and batch segment); k_mlp_forward
+// on 49,760 rows 12.3 us (58).  A training step is then paced by its three
+// launches.
 #include <cmath>
+#include <cstdint>
 #include <mutex>
 
 #include "handle.h"
@@ -30,153 +45,257 @@ constexpr int WH1 = 0, WH2 = WH1 + NH, WD1 = WH2 + NH, WD2 = WD1 + NH, WD3 = WD2
               WL = WD3 + NO, WN = WL + 1;
 static_assert(WN == SEM_MLP_WORK, "workspace per sample");
 
-__device__ __forceinline__ void stage_params(const float* __restrict__ p, float* sp) {
-    for (int r = threadIdx.x; r < NP; r += blockDim.x) sp[r] = p[r];
-    __syncthreads();
+constexpr int TS = 16;             // samples per tile
+constexpr int HS = NH + 4;         // LDS row stride of a sample's hidden values
+
+using f4 = __attribute__((ext_vector_type(4))) float;
+using d4 = __attribute__((ext_vector_type(4))) double;
+
+// four consecutive floats: one 16-byte access where the caller's array is
+// 16-byte aligned (AL), else four of 4 bytes (a view into a larger array)
+template <bool AL>
+__device__ __forceinline__ f4 ld4(const float* __restrict__ p) {
+    if constexpr (AL) return *reinterpret_cast<const f4*>(p);
+    else return f4{p[0], p[1], p[2], p[3]};
+}
+template <bool AL>
+__device__ __forceinline__ void st4(float* __restrict__ p, f4 v) {
+    if constexpr (AL) *reinterpret_cast<f4*>(p) = v;
+    else { p[0] = v[0]; p[1] = v[1]; p[2] = v[2]; p[3] = v[3]; }
 }
 
-// hidden layers and logits of one sample
-__device__ __forceinline__ void forward_one(const float* sp, const float* __restrict__ xin,
-                                            float* h1, float* h2, float* z3) {
-    float x[NI];
+// lane = 16 g + c of wave w.  A operand of a step: row c, k = g; B: k = g,
+// column c; accumulator: rows 4 g + 0..3, column c.  The k of the steps are
+// taken as 16 t + 4 g + s (any order will do), so that a lane's four steps of
+// one t are four consecutive floats.
+struct Lane { int w, g, c; };
+__device__ __forceinline__ Lane lane_of(int t) { return {t >> 6, (t >> 4) & 3, t & 15}; }
+
+// this lane's share of the parameters
+struct Weights {
+    f4 w1, b1, w2[4], b2, w3[NO];
+    float b3[NO];
+    template <bool AL>
+    __device__ __forceinline__ void load(const float* __restrict__ p, Lane l) {
+        const int row = 16 * l.w + l.c, r4 = 16 * l.w + 4 * l.g;
+        w1 = ld4<AL>(p + OW1 + row * NI + 4 * l.g);
+        b1 = ld4<AL>(p + OB1 + r4);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) x[i] = xin[i];
+        for (int t = 0; t < 4; ++t) w2[t] = ld4<AL>(p + OW2 + row * NH + 16 * t + 4 * l.g);
+        b2 = ld4<AL>(p + OB2 + r4);
 #pragma unroll
-    for (int o = 0; o < NH; ++o) {
-        float s = sp[OB1 + o];
+        for (int o = 0; o < NO; ++o) {
+            w3[o] = ld4<AL>(p + OW3 + o * NH + r4);
+            b3[o] = p[OB3 + o];
+        }
+    }
+};
+
+struct Tile {
+    float h1[TS][HS];              // first hidden layer, then reused for d2
+    float z[4][NO][TS];            // the waves' parts of the logits
+};
+
+// Hidden values of units 16w + 4g + 0..3 of sample c, and its logits (every
+// lane of column c holds them).  Two barriers; the tile may be written again
+// after the second.
+__device__ __forceinline__ void forward_tile(const Weights& W, f4 x, Lane l, Tile& T, f4& h1, f4& h2,
+                                             float* z3) {
+    f4 a = W.b1;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) s = fmaf(sp[OW1 + o * NI + i], x[i], s);
-        h1[o] = tanhf(s);
+    for (int s = 0; s < 4; ++s) a = __builtin_amdgcn_mfma_f32_16x16x4f32(W.w1[s], x[s], a, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h1[r] = tanhf(a[r]);
+    st4<true>(&T.h1[l.c][16 * l.w + 4 * l.g], h1);
+    __syncthreads();
+    a = W.b2;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const f4 h = ld4<true>(&T.h1[l.c][16 * t + 4 * l.g]);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a = __builtin_amdgcn_mfma_f32_16x16x4f32(W.w2[t][s], h[s], a, 0, 0, 0);
     }
 #pragma unroll
-    for (int o = 0; o < NH; ++o) {
-        float s = sp[OB2 + o];
-#pragma unroll
-        for (int h = 0; h < NH; ++h) s = fmaf(sp[OW2 + o * NH + h], h1[h], s);
-        h2[o] = tanhf(s);
-    }
+    for (int r = 0; r < 4; ++r) h2[r] = tanhf(a[r]);
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
-        float s = sp[OB3 + o];
+        float s = 0.0f;
 #pragma unroll
-        for (int h = 0; h < NH; ++h) s = fmaf(sp[OW3 + o * NH + h], h2[h], s);
-        z3[o] = s;
+        for (int r = 0; r < 4; ++r) s = fmaf(W.w3[o][r], h2[r], s);
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (l.g == 0) T.z[l.w][o][l.c] = s;
     }
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < NO; ++o)
+        z3[o] = W.b3[o] + ((T.z[0][o][l.c] + T.z[1][o][l.c]) + (T.z[2][o][l.c] + T.z[3][o][l.c]));
 }
 
 }  // namespace
 
+template <bool AL>
 __global__ void __launch_bounds__(256)
 k_mlp_forward(const float* __restrict__ p, const float* __restrict__ x, int64_t n,
               float* __restrict__ logits) {
-    __shared__ float sp[NP];
-    stage_params(p, sp);
-    for (int64_t b = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; b < n;
-         b += int64_t(gridDim.x) * blockDim.x) {
-        float h1[NH], h2[NH], z3[NO];
-        forward_one(sp, x + b * NI, h1, h2, z3);
-#pragma unroll
-        for (int o = 0; o < NO; ++o) logits[b * NO + o] = z3[o];
+    __shared__ Tile T;
+    const Lane l = lane_of(threadIdx.x);
+    Weights W;
+    W.load<AL>(p, l);
+    const int64_t nt = (n + TS - 1) / TS;
+    for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+        const int64_t b = t * TS + l.c;
+        f4 h1, h2;
+        float z3[NO];
+        forward_tile(W, ld4<AL>(x + min(b, n - 1) * NI + 4 * l.g), l, T, h1, h2, z3);
+        if (l.w == 0 && l.g < NO && b < n) logits[b * NO + l.g] = l.g == 0 ? z3[0] : l.g == 1 ? z3[1] : z3[2];
     }
 }
 
+template <bool AL>
 __global__ void __launch_bounds__(256)
 k_mlp_samples(const float* __restrict__ p, const float* __restrict__ x,
               const int8_t* __restrict__ cls, const int32_t* __restrict__ idx, int64_t n,
               int64_t n_rows, float* __restrict__ work) {
-    __shared__ float sp[NP];
-    stage_params(p, sp);
+    __shared__ Tile T;
+    const Lane l = lane_of(threadIdx.x);
     const float inv_n = 1.0f / float(n);
-    for (int64_t b = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; b < n;
-         b += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t s = idx ? min(max(int64_t(idx[b]), int64_t(0)), n_rows - 1) : b;
-        float h1[NH], h2[NH], z3[NO];
-        forward_one(sp, x + s * NI, h1, h2, z3);
-        const int lab = min(max(int(cls[s]), 0), NO - 1);
-        // softmax and cross-entropy
-        float zm = fmaxf(z3[0], fmaxf(z3[1], z3[2]));
-        float ex[NO], se = 0.0f;
+    Weights W;
+    W.load<AL>(p, l);
+    // the second layer transposed: row 16w + c of W2^T
+    float wt[16];
 #pragma unroll
-        for (int o = 0; o < NO; ++o) { ex[o] = expf(z3[o] - zm); se += ex[o]; }
-        float* wb = work + b * WN;
-        float d3[NO];
+    for (int k = 0; k < 16; ++k) wt[k] = p[OW2 + (16 * (k / 4) + 4 * l.g + k % 4) * NH + 16 * l.w + l.c];
+    const int64_t nt = (n + TS - 1) / TS;
+    for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+        const int64_t b = t * TS + l.c, bc = min(b, n - 1);
+        const int64_t s = idx ? min(max(int64_t(idx[bc]), int64_t(0)), n_rows - 1) : bc;
+        const int lab = min(max(int(cls[s]), 0), NO - 1);
+        f4 h1, h2;
+        float z3[NO];
+        forward_tile(W, ld4<AL>(x + s * NI + 4 * l.g), l, T, h1, h2, z3);
+        // softmax and cross-entropy
+        const float zm = fmaxf(z3[0], fmaxf(z3[1], z3[2]));
+        float ex[NO], se = 0.0f, zl = z3[0];
 #pragma unroll
         for (int o = 0; o < NO; ++o) {
-            d3[o] = (ex[o] / se - (o == lab ? 1.0f : 0.0f)) * inv_n;
-            wb[WD3 + o] = d3[o];
+            ex[o] = expf(z3[o] - zm);
+            se += ex[o];
+            if (o == lab) zl = z3[o];
         }
-        wb[WL] = -(z3[lab] - zm - logf(se));
-        // layer 2 error: (W3^T d3) * (1 - h2^2)
-        float d2[NH];
+        float d3[NO];
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
+        for (int o = 0; o < NO; ++o) d3[o] = (ex[o] / se - (o == lab ? 1.0f : 0.0f)) * inv_n;
+        // layer 2 error: (W3^T d3) * (1 - h2^2)
+        f4 d2;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
             float s2 = 0.0f;
 #pragma unroll
-            for (int o = 0; o < NO; ++o) s2 = fmaf(sp[OW3 + o * NH + h], d3[o], s2);
-            d2[h] = s2 * (1.0f - h2[h] * h2[h]);
-            wb[WH2 + h] = h2[h];
-            wb[WD2 + h] = d2[h];
+            for (int o = 0; o < NO; ++o) s2 = fmaf(W.w3[o][r], d3[o], s2);
+            d2[r] = s2 * (1.0f - h2[r] * h2[r]);
         }
+        const int r4 = 16 * l.w + 4 * l.g;
+        st4<true>(&T.h1[l.c][r4], d2);
+        __syncthreads();
         // layer 1 error: (W2^T d2) * (1 - h1^2)
+        f4 a = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            float s1 = 0.0f;
+        for (int k = 0; k < 4; ++k) {
+            const f4 d = ld4<true>(&T.h1[l.c][16 * k + 4 * l.g]);
 #pragma unroll
-            for (int o = 0; o < NH; ++o) s1 = fmaf(sp[OW2 + o * NH + h], d2[o], s1);
-            wb[WH1 + h] = h1[h];
-            wb[WD1 + h] = s1 * (1.0f - h1[h] * h1[h]);
+            for (int q = 0; q < 4; ++q) a = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[4 * k + q], d[q], a, 0, 0, 0);
+        }
+        __syncthreads();               // the tile is written again by the next samples
+        if (b >= n) continue;
+        f4 d1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d1[r] = a[r] * (1.0f - h1[r] * h1[r]);
+        float* wb = work + b * WN;
+        st4<AL>(wb + WH1 + r4, h1);
+        st4<AL>(wb + WH2 + r4, h2);
+        st4<AL>(wb + WD1 + r4, d1);
+        st4<AL>(wb + WD2 + r4, d2);
+        if (l.w == 0 && l.g == 0) {
+#pragma unroll
+            for (int o = 0; o < NO; ++o) wb[WD3 + o] = d3[o];
+            wb[WL] = -(zl - zm - logf(se));
         }
     }
 }
 
-// gradient of every parameter (and, in the last slot, the mean loss) as a
-// batch sum: a workgroup owns 64 consecutive slots and splits the batch into
-// 16 interleaved segments (b = seg, seg + 16, ...), each summed in sample
-// order in double; the 16 partial sums are then added in segment order, so
-// the result does not depend on scheduling.
-constexpr int GRAD_SLOTS = 64, GRAD_SEGS = 16;
+// Gradients as batch sums, and the mean loss.  A workgroup per 16 x 16 tile:
+// 0-15 of W2 (rows d2, columns h1), 16-19 of W1 (d1, x), 20-23 of W3 (d3 and,
+// as a fourth row, the loss; columns h2; 12 rows idle).  The biases and the
+// loss are the row sums of the same operand, formed by the first tile of each
+// row.  A wave takes every 16th group of four samples in order; the 16 waves'
+// parts are added in wave order, so the result does not depend on scheduling.
+constexpr int GRAD_TILES = 24, GRAD_WAVES = 16, GRAD_THREADS = 64 * GRAD_WAVES;
 
-__global__ void __launch_bounds__(GRAD_SLOTS * GRAD_SEGS)
+__global__ void __launch_bounds__(GRAD_THREADS)
 k_mlp_grad(const float* __restrict__ x, const int32_t* __restrict__ idx, int64_t n,
            int64_t n_rows, const float* __restrict__ work, float* __restrict__ grad,
            float* __restrict__ loss) {
-    __shared__ double part[GRAD_SEGS][GRAD_SLOTS];
-    const int q = threadIdx.x % GRAD_SLOTS, seg = threadIdx.x / GRAD_SLOTS;
-    const int r = blockIdx.x * GRAD_SLOTS + q;
-    double s = 0.0;
-    if (r == NP) {                       // mean loss
-        for (int64_t b = seg; b < n; b += GRAD_SEGS) s += work[b * WN + WL];
-    } else if (r < OB1) {                // W1[o][i] = sum d1[o] x[i]
-        const int o = r / NI, i = r % NI;
-        for (int64_t b = seg; b < n; b += GRAD_SEGS) {
-            const int64_t sm = idx ? min(max(int64_t(idx[b]), int64_t(0)), n_rows - 1) : b;
-            s += double(work[b * WN + WD1 + o]) * double(x[sm * NI + i]);
+    __shared__ double part[GRAD_WAVES][256];
+    __shared__ double rowsum[GRAD_WAVES][64];
+    const int q = threadIdx.x, v = q >> 6, l = q & 63, g = l >> 4, c = l & 15;
+    const int tile = blockIdx.x;
+    const int kind = tile < 16 ? 2 : tile < 20 ? 1 : 3;          // weight matrix
+    const int rb = kind == 2 ? tile / 4 : kind == 1 ? tile - 16 : 0;
+    const int cb = kind == 2 ? tile % 4 : kind == 1 ? 0 : tile - 20;
+    const int oa = kind == 2 ? WD2 + 16 * rb + c : kind == 1 ? WD1 + 16 * rb + c : WD3 + min(c, 3);
+    const int ob = kind == 2 ? WH1 + 16 * cb + c : WH2 + 16 * cb + c;
+    const bool row_ok = kind != 3 || c < 4;
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    double rs = 0.0;
+    const int64_t ns = (n + 3) / 4;
+    // sixteen groups' operands are requested together: one at a time the loop
+    // waits a round trip per group (14 against 11 us at 1024 samples)
+    constexpr int U = 16;
+    for (int64_t st = v; st < ns; st += U * GRAD_WAVES) {
+        float av[U], bv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t bc = min(4 * (st + u * GRAD_WAVES) + g, n - 1);
+            const float* wb = work + bc * WN;
+            av[u] = wb[oa];
+            if (kind == 1) {
+                const int64_t sm = idx ? min(max(int64_t(idx[bc]), int64_t(0)), n_rows - 1) : bc;
+                bv[u] = x[sm * NI + c];
+            } else {
+                bv[u] = wb[ob];
+            }
         }
-    } else if (r < OW2) {                // b1[o] = sum d1[o]
-        const int o = r - OB1;
-        for (int64_t b = seg; b < n; b += GRAD_SEGS) s += work[b * WN + WD1 + o];
-    } else if (r < OB2) {                // W2[o][h] = sum d2[o] h1[h]
-        const int o = (r - OW2) / NH, h = (r - OW2) % NH;
-        for (int64_t b = seg; b < n; b += GRAD_SEGS)
-            s += double(work[b * WN + WD2 + o]) * double(work[b * WN + WH1 + h]);
-    } else if (r < OW3) {                // b2[o] = sum d2[o]
-        const int o = r - OB2;
-        for (int64_t b = seg; b < n; b += GRAD_SEGS) s += work[b * WN + WD2 + o];
-    } else if (r < OB3) {                // W3[o][h] = sum d3[o] h2[h]
-        const int o = (r - OW3) / NH, h = (r - OW3) % NH;
-        for (int64_t b = seg; b < n; b += GRAD_SEGS)
-            s += double(work[b * WN + WD3 + o]) * double(work[b * WN + WH2 + h]);
-    } else if (r < NP) {                 // b3[o] = sum d3[o]
-        const int o = r - OB3;
-        for (int64_t b = seg; b < n; b += GRAD_SEGS) s += work[b * WN + WD3 + o];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // past the batch both operands are zero (no 0 * inf)
+            const bool in = 4 * (st + u * GRAD_WAVES) + g < n;
+            const double da = (in && row_ok) ? double(av[u]) : 0.0, db = in ? double(bv[u]) : 0.0;
+            rs += da;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(da, db, acc, 0, 0, 0);
+        }
     }
-    part[seg][q] = s;
+    // accumulator: rows 4 r + g, column c
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[v][16 * (4 * r + g) + c] = acc[r];
+    rowsum[v][l] = rs;
     __syncthreads();
-    if (seg == 0 && r <= NP) {
+    if (q < 256) {
         double t = 0.0;
-        for (int k = 0; k < GRAD_SEGS; ++k) t += part[k][q];
-        if (r == NP) *loss = float(t / double(n));
-        else grad[r] = float(t);
+        for (int k = 0; k < GRAD_WAVES; ++k) t += part[k][q];
+        const int i = q >> 4, j = q & 15;
+        if (kind == 2) grad[OW2 + (16 * rb + i) * NH + 16 * cb + j] = float(t);
+        else if (kind == 1) grad[OW1 + (16 * rb + i) * NI + j] = float(t);
+        else if (i < NO) grad[OW3 + i * NH + 16 * cb + j] = float(t);
+    } else if (q < 256 + 16 && cb == 0) {
+        const int i = q - 256;
+        double t = 0.0;
+        for (int k = 0; k < GRAD_WAVES; ++k)
+            for (int h = 0; h < 4; ++h) t += rowsum[k][16 * h + i];
+        if (kind == 2) grad[OB2 + 16 * rb + i] = float(t);
+        else if (kind == 1) grad[OB1 + 16 * rb + i] = float(t);
+        else if (i < NO) grad[OB3 + i] = float(t);
+        else if (i == NO) *loss = float(t / double(n));
     }
 }
 
@@ -223,11 +342,30 @@ int scratch_for_current_device(float** out) {
     return SEM_OK;
 }
 
+// tiles of 16 samples, at most eight workgroups per CU of a 256-CU GPU: each
+// loads the 22 KB of parameters into its registers once
 int grid_of(int64_t n) {
-    int64_t g = (n + 255) / 256;
-    if (g < 1) g = 1;
-    if (g > 65536) g = 65536;
-    return int(g);
+    const int64_t g = (n + sem::TS - 1) / sem::TS;
+    return int(g < 1 ? 1 : g > 2048 ? 2048 : g);
+}
+
+bool aligned16(const void* a, const void* b, const void* c) {
+    return ((uintptr_t(a) | uintptr_t(b) | uintptr_t(c)) & 15) == 0;
+}
+
+int launch_backward(const float* p, const float* x, int64_t n_rows, const int8_t* cls,
+                    const int32_t* idx, int64_t n, float* work, float* grad, float* loss, hipStream_t s) {
+    if (aligned16(p, x, work))
+        hipLaunchKernelGGL(sem::k_mlp_samples<true>, dim3(grid_of(n)), dim3(256), 0, s, p, x, cls, idx, n,
+                           n_rows, work);
+    else
+        hipLaunchKernelGGL(sem::k_mlp_samples<false>, dim3(grid_of(n)), dim3(256), 0, s, p, x, cls, idx, n,
+                           n_rows, work);
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(sem::k_mlp_grad, dim3(sem::GRAD_TILES), dim3(sem::GRAD_THREADS), 0, s, x, idx, n,
+                       n_rows, work, grad, loss);
+    HIPCHK(hipGetLastError());
+    return SEM_OK;
 }
 }  // namespace
 
@@ -237,8 +375,11 @@ static int mlp_forward_impl(const float* p, const float* x, int64_t n, float* lo
     if (!p || !logits || (n > 0 && !x)) return fail(SEM_ERR_ARG, "null array");
     if (n < 0) return fail(SEM_ERR_ARG, "negative sample count");
     if (n == 0) return SEM_OK;
-    hipLaunchKernelGGL(sem::k_mlp_forward, dim3(grid_of(n)), dim3(256), 0, (hipStream_t)stream,
-                       p, x, n, logits);
+    hipStream_t s = (hipStream_t)stream;
+    if (aligned16(p, x, nullptr))
+        hipLaunchKernelGGL(sem::k_mlp_forward<true>, dim3(grid_of(n)), dim3(256), 0, s, p, x, n, logits);
+    else
+        hipLaunchKernelGGL(sem::k_mlp_forward<false>, dim3(grid_of(n)), dim3(256), 0, s, p, x, n, logits);
     HIPCHK(hipGetLastError());
     return SEM_OK;
 }
@@ -252,14 +393,7 @@ static int mlp_backward_impl(const float* p, const float* x, int64_t n_rows, con
     if (!p || !x || !cls || !work || !grad || !loss) return fail(SEM_ERR_ARG, "null array");
     if (n < 1) return fail(SEM_ERR_ARG, "empty batch");
     if (n_rows < 1 || (!idx && n > n_rows)) return fail(SEM_ERR_ARG, "batch larger than the data");
-    hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(sem::k_mlp_samples, dim3(grid_of(n)), dim3(256), 0, s, p, x, cls, idx, n,
-                       n_rows, work);
-    HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(sem::k_mlp_grad, dim3((SEM_MLP_NPARAM + 1 + sem::GRAD_SLOTS - 1) / sem::GRAD_SLOTS),
-                       dim3(sem::GRAD_SLOTS * sem::GRAD_SEGS), 0, s, x, idx, n, n_rows, work, grad, loss);
-    HIPCHK(hipGetLastError());
-    return SEM_OK;
+    return launch_backward(p, x, n_rows, cls, idx, n, work, grad, loss, (hipStream_t)stream);
 }
 
 int mlp_backward(const float* p, const float* x, int64_t n_rows, const int8_t* cls,
@@ -281,14 +415,7 @@ static int mlp_backward_noalloc_impl(const float* p, const float* x, int64_t n_r
     // the same two kernels as mlp_backward; k_mlp_samples writes every
     // workspace entry that k_mlp_grad reads (the first n samples), so nothing
     // left by an earlier call is read and no clearing is needed
-    hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(sem::k_mlp_samples, dim3(grid_of(n)), dim3(256), 0, s, p, x, cls, idx, n,
-                       n_rows, work);
-    HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(sem::k_mlp_grad, dim3((SEM_MLP_NPARAM + 1 + sem::GRAD_SLOTS - 1) / sem::GRAD_SLOTS),
-                       dim3(sem::GRAD_SLOTS * sem::GRAD_SEGS), 0, s, x, idx, n, n_rows, work, grad, loss);
-    HIPCHK(hipGetLastError());
-    return SEM_OK;
+    return launch_backward(p, x, n_rows, cls, idx, n, work, grad, loss, (hipStream_t)stream);
 }
 
 int mlp_backward_noalloc(const float* p, const float* x, int64_t n_rows, const int8_t* cls,
