@@ -91,7 +91,7 @@ def cpu_baseline(plan=(("vortex_8x8x4_n4", 10), (WORKLOAD, 3))):
 def kernel_source_hash():
     """Hash of the fused-stage kernel source (to detect stale counter data)."""
     h = hashlib.sha256()
-    for f in ("stage_fused.hip", "stage_fused.h", "devmesh.h"):
+    for f in ("stage_fused.hip", "stage_own.hip", "stage_fused.h", "devmesh.h", "nodeval.h"):
         with open(os.path.join(ROOT, "paper_2410_21607_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -130,15 +130,26 @@ def column_instance(N, lpc, layout, fp64, diss_inline):
             f"{'true' if diss_inline else 'false'}, {order}>")
 
 
+def stage_instance(N, lpc, layout, fp64, diss_inline):
+    """Name (or its start) of the kernel instance that a box-element stage of a
+    uniform mesh runs: the owner kernel (template arguments: N + 1, its own
+    layers per chunk) in FP64 without dissipation at N >= 2, else the column
+    kernel; None for the block layout."""
+    if fp64 and not diss_inline and N >= 2 and layout in (0, 2, 3):
+        return f"k_stage_own<{N + 1}, "
+    return column_instance(N, lpc, layout, fp64, diss_inline)
+
+
 def traffic_from_counters(fetch_csv, write_csv, workload=WORKLOAD, launches_per_stage=4, out_dir=None):
     """Write profiles/traffic_<workload>.json from two rocprofv3 counter runs
     of ``bench.py --copy-calibration`` on this workload: ``--pmc FETCH_SIZE``
     then ``--pmc WRITE_SIZE`` (KiB per dispatch).  Each counter is scaled by
     what it reads for the calibration kernel (torch's elementwise multiply,
-    which reads and writes one state-sized array of known size); the column
+    which reads and writes one state-sized array of known size); the stage
     kernel's figure is the median per dispatch of its most frequent instance
-    (the one the bench times) times the launches of one stage (four colours on
-    a uniform periodic mesh).  Runs on the host only."""
+    (the one the bench times) times the launches of one stage (one of the owner
+    kernel, four colours of the column kernel on a uniform periodic mesh).
+    Runs on the host only."""
     import csv
     import statistics
     import numpy as np
@@ -160,12 +171,15 @@ def traffic_from_counters(fetch_csv, write_csv, workload=WORKLOAD, launches_per_
     fetch, write = per_kernel(fetch_csv, "FETCH_SIZE"), per_kernel(write_csv, "WRITE_SIZE")
     # the multiply is the most frequent elementwise kernel of such a run
     calib = [k for k in fetch if "elementwise_kernel" in k and "Unary" in k]
-    cols = [k for k in fetch if "k_stage_columns" in k]
+    stage = ("k_stage_columns", "k_stage_own")
+    cols = [k for k in fetch if any(n in k for n in stage)]
     if not calib or not cols:
         raise ValueError("counter files hold no calibration kernel or no column kernel")
     calib_k = max(calib, key=lambda k: len(fetch[k]))
     main_k = max(cols, key=lambda k: len(fetch[k]))
-    main_w = max((k for k in write if "k_stage_columns" in k), key=lambda k: len(write[k]), default=None)
+    if "k_stage_own" in main_k:
+        launches_per_stage = 1
+    main_w = max((k for k in write if any(n in k for n in stage)), key=lambda k: len(write[k]), default=None)
     if main_w != main_k:
         raise ValueError("the FETCH_SIZE and WRITE_SIZE runs timed different column kernels "
                          f"({main_k} / {main_w}); pin the layout with --layout")
@@ -747,7 +761,7 @@ def main():
         for _ in range(5):
             torch.mul(src, 1.0, out=dst)
         torch.cuda.synchronize()
-    traffic = measured_traffic(args.workload, column_instance(
+    traffic = measured_traffic(args.workload, stage_instance(
         case["N"], lpc, layout, prec == api.SEM_FP64,
         bool(args.dissipation) and prec == api.SEM_FP64 and layout != api.SEM_LAYOUT_BLOCKS))
     stages = 3 * n_steps

@@ -271,7 +271,12 @@ int sem_stage_update(const sem_mesh *mesh, double a, double b, double c,
 
 /* Fused stage: d_qout = a*d_qn + b*d_qs + c*R(d_qs), with R the full
  * right-hand side (scatter, element RHS, assembly, gather, finalize, lid rule)
- * evaluated without storing element-local data.  Work units (columns, or
+ * evaluated without storing element-local data.  In the column layouts an FP64
+ * stage on box elements without dissipation (N >= 2, within 2 GiB of state;
+ * N = 7 up to 768 columns) computes every node whose columns have one level
+ * and surround it in one launch, by the one column that owns it; the columns
+ * of the other nodes and the pass that sums theirs are two more launches.
+ * Everywhere else work units (columns, or
  * 2 x 2 column blocks: sem_stage_set_layout) are coloured so that units of
  * one colour share no node; the launches of one colour cover the units of
  * every refinement level of that colour (a workgroup marches up one column
@@ -289,7 +294,8 @@ int sem_stage(const sem_mesh *mesh, double a, double b, double c,
               int precision, void *stream);
 
 /* Work decomposition of sem_stage (chosen by the autotuner, or by hand):
- * layers_per_chunk = stacked elements handled by one workgroup, one thread per
+ * layers_per_chunk = stacked elements handled by one workgroup of the coloured
+ * launches (the owning columns' launch has its own), one thread per
  * unique node of the chunk ((N+1)^2 (layers_per_chunk N + 1) threads).
  * 0 = default (the deepest chunk of at most 512 threads).  Supported: 1, 2, 4
  * and 8 at N <= 4, 1, 2 and 4 at N = 5, 1 and 2 at N = 6, 7, and 1 at N = 8
@@ -336,8 +342,9 @@ int sem_stage_get_layout(const sem_mesh *mesh, int *layout, int *param);
 /* Autotuner: times every supported work layout on this mesh (the column
  * layout at each supported layers_per_chunk, in FP64 in each thread order,
  * the block layout at 1, 2, 4, ... vertical segments; reps fused stages
- * each, HIP events on `stream`, d_qout used as scratch), keeps the fastest
- * with sem_stage_set_layout, and reports
+ * each, HIP events on `stream`, d_qout used as scratch; the default column
+ * layout alone of the column ones where sem_stage needs no coloured launches),
+ * keeps the fastest with sem_stage_set_layout, and reports
  * it (*best_lpc = the column layout's layers per chunk, see
  * sem_stage_get_layout for the layout; *best_ms = mean stage time in ms;
  * either may be NULL).  Synchronises the stream. */

@@ -25,6 +25,8 @@ struct DevMesh {
     const double *D, *w;      // LGL derivative matrix and weights
     const double *rho0, *theta0, *dth0, *p0;   // reference state per kz
     const double *inv_rho0, *inv_theta0;       // their reciprocals per kz
+    const double* lev;  // [7][nzn]: rho0, 1/rho0, 1/theta0, p0, dtheta0/dz, the lower element's share of
+                        // a plane between two (by their depths), 2/dz per layer
     double binom[11];   // binom[n] = C(gamma, n): Taylor coefficients of (1+x)^gamma
     // optional dissipation (sem_mesh_set_dissipation): Smagorinsky constant
     // (0 = off), absorbing-layer rate per kz (null = off), and the assembled

@@ -1,6 +1,7 @@
 // Device helpers shared by the HIP translation units: the value of one field
 // at an element-local horizontal slot (through the hanging rows when the slot
-// is a hanging point) and the column rule of the refinement flags.
+// is a hanging point), the column rule of the refinement flags and the
+// pressure ratio.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -48,6 +49,25 @@ __device__ __forceinline__ int8_t column_rule(const DevMesh& m, const int8_t* __
         if (ok) return -1;
     }
     return 0;
+}
+
+// (1+x)^gamma - 1 for the ideal-gas pressure ratio.  For |x| <= 1/64 the
+// Taylor polynomial sum_{n=1..10} C(gamma, n) x^n is used (the first neglected
+// term is below 2^-66 |gamma x|, far under one ulp); otherwise
+// expm1(gamma log1p(x)).  That general branch is kept out of line: inlined,
+// the compiler hoists its polynomial constants out of the chunk loop, where
+// they hold about 30 registers for the whole kernel.
+static __device__ __noinline__ double pow1p_minus1_far(double x, double gamma) {
+    return expm1(gamma * log1p(x));
+}
+__device__ __forceinline__ double pow1p_minus1_near(const DevMesh& m, double x) {
+    double s = m.binom[10];
+#pragma unroll
+    for (int n = 9; n >= 1; --n) s = s * x + m.binom[n];
+    return s * x;
+}
+__device__ __forceinline__ double pow1p_minus1(const DevMesh& m, double x) {
+    return fabs(x) <= 1.0 / 64.0 ? pow1p_minus1_near(m, x) : pow1p_minus1_far(x, m.gamma);
 }
 
 }  // namespace sem

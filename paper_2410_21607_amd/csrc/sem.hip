@@ -814,12 +814,21 @@ static int sem_mesh_set_reference_impl(sem_mesh* M, const double* rho0, const do
         ir[k] = 1.0 / r[k];
         it[k] = 1.0 / t[k];
     }
-    const std::vector<double>* src[6] = {&r, &t, &dt, &p0, &ir, &it};
-    const double** dst[6] = {&M->d.rho0, &M->d.theta0, &M->d.dth0, &M->d.p0, &M->d.inv_rho0,
-                             &M->d.inv_theta0};
-    for (int q = 0; q < 6; ++q) {
+    // the tables the owner kernel reads, row by row
+    std::vector<double> lev;
+    lev.reserve(size_t(7) * H.nzn);
+    for (const auto* row : {&r, &ir, &it, &p0, &dt}) lev.insert(lev.end(), row->begin(), row->end());
+    lev.resize(size_t(7) * H.nzn, 0.0);
+    for (int el = 0; el < H.n_z; ++el) {
+        if (el > 0) lev[size_t(5) * H.nzn + el * H.N] = H.dz[el - 1] / (H.dz[el - 1] + H.dz[el]);
+        lev[size_t(6) * H.nzn + el] = H.sz[el];
+    }
+    const std::vector<double>* src[7] = {&r, &t, &dt, &p0, &ir, &it, &lev};
+    const double** dst[7] = {&M->d.rho0, &M->d.theta0, &M->d.dth0, &M->d.p0, &M->d.inv_rho0,
+                             &M->d.inv_theta0, &M->d.lev};
+    for (int q = 0; q < 7; ++q) {
         if (M->have_ref) {
-            HIPCHK(hipMemcpy((void*)*dst[q], src[q]->data(), H.nzn * 8, hipMemcpyHostToDevice));
+            HIPCHK(hipMemcpy((void*)*dst[q], src[q]->data(), src[q]->size() * 8, hipMemcpyHostToDevice));
         } else {
             int rc = M->upload(*src[q], dst[q]);
             if (rc != SEM_OK) return rc;
@@ -1203,7 +1212,11 @@ static int sem_stage_autotune_impl(sem_mesh* M, const double* qn, const double* 
     // each thread order (float runs the natural order in any); column
     // blocks in 1, 2, 4, ... vertical segments (distinct segment lengths)
     std::vector<std::pair<int, int>> cand;
-    for (int lpc = 1; lpc <= 16; lpc *= 2)
+    // where the owner kernel runs, chunks and orders concern the columns of
+    // the irregular nodes alone: one candidate, the default
+    const bool own = sem::own_used(M->d, prec);
+    if (own) cand.push_back({SEM_LAYOUT_COLUMNS, 0});
+    for (int lpc = 1; lpc <= 16 && !own; lpc *= 2)
         if (sem::fused_lpc_supported(M->host.N, lpc) && lpc <= 2 * M->host.n_z) {
             cand.push_back({SEM_LAYOUT_COLUMNS, lpc});
             if (prec == SEM_FP64) {
@@ -1225,7 +1238,7 @@ static int sem_stage_autotune_impl(sem_mesh* M, const double* qn, const double* 
     float best_t = 0.0f;
     for (size_t ci = 0; ci < cand.size(); ++ci) {
         sem::FusedPlan P;
-        if (sem::fused_plan_build(M->host, cand[ci].first, cand[ci].second, P) != SEM_OK) {
+        if (sem::fused_plan_build(M->host, cand[ci].first, cand[ci].second, P, own) != SEM_OK) {
             sem::fused_plan_free(P);
             continue;
         }

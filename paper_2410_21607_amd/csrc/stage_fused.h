@@ -82,12 +82,37 @@ struct BlockTables {
     int n_seg, Ls;              // vertical segments, layers per segment
 };
 
+// Owner kernel: regular nodes, each computed whole by one column.  A node is
+// regular when every column sharing it has the same level and the columns
+// surround it completely (one inside a column, two at a face, four at a
+// corner) and no hanging point takes its value from it; its owner is the
+// column that has it at a position i < N, j < N.  `map` lists per column the
+// positions the kernel loads (unique node or -(hh + 1)): the owned N x N
+// (i + N j), the upper faces (N, j) and (i, N), then the halo lines, N
+// positions each: per j the left neighbour's (i, j), per i the lower
+// neighbour's (i, j).  The nodes that are not regular are left to the side
+// columns and the tail.
+constexpr int own_owned(int N) { return N * N; }
+constexpr int own_positions(int N) { return 3 * N * N + 2 * N; }
+struct OwnTables {
+    const int32_t* map;         // n * own_positions(N)
+    const double* sxy;          // n * (2/dx, 2/dy)
+    const uint64_t* mask;       // n: bit i + N j, the node is regular
+    const uint8_t* hang;        // n: some position of `map` hangs
+    int n;
+};
+
 // Owns the device memory of the tables.
 struct FusedPlan {
     FusedTables t{};                      // column layout (every column)
     std::vector<int32_t> color_ptr_host;
     TailTables tail{};                    // column layout with side columns
     bool has_tail = false;
+    bool own = false;                     // tables of the owner kernel (own_used: whether a stage runs it)
+    OwnTables ot{};
+    FusedTables to{};                     // its side columns (one launch) and their tail
+    TailTables own_tail{};
+    int n_side = 0;
     int layout = 0;                       // SEM_LAYOUT_COLUMNS, _COLUMNS_KZ, _COLUMNS_SPLIT or _BLOCKS
     BlockTables bt{};                     // block layout
     FusedTables ts{};                     // block layout: the columns in no block
@@ -98,8 +123,9 @@ struct FusedPlan {
 };
 // layout SEM_LAYOUT_COLUMNS / _COLUMNS_KZ / _COLUMNS_SPLIT: param = layers per
 // chunk (0 = default);
-// SEM_LAYOUT_BLOCKS: param = vertical segments (0 = default)
-int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& plan);
+// SEM_LAYOUT_BLOCKS: param = vertical segments (0 = default).  owner: with the
+// owner kernel's tables where it applies.
+int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& plan, bool owner = true);
 void fused_plan_free(FusedPlan& plan);
 bool fused_lpc_supported(int N, int layers_per_chunk);
 // whether the split-element thread order applies (two or more layers per
@@ -110,6 +136,18 @@ bool fused_blocks_supported(const HostMesh& H);
 // Whether sem_stage evaluates the optional dissipation inside the column
 // kernel (FP64, box elements, column layout) instead of a pre-pass.
 bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& plan, int precision);
+
+// The owner kernel: whether it has an instance of order N; whether it is the
+// faster one for a mesh of n_col columns (its plans then hold its tables);
+// whether a mesh is within its limits (32-bit offsets of the state, the level
+// table in LDS); whether a column-layout stage runs it; its launch over the
+// plan's regular nodes.
+bool own_supported(int N);
+bool own_applies(int N, int n_col);
+bool own_fits(const DevMesh& m);
+bool own_used(const DevMesh& m, int precision);
+int own_launch(const DevMesh& m, const OwnTables& ot, double a, double b, double c, const double* qn,
+               const double* qs, double* qout, hipStream_t stream);
 
 // Launches the column kernel and the shared-node kernel on `stream`.
 int fused_stage_launch(const DevMesh& m, const FusedPlan& plan, double a, double b, double c,

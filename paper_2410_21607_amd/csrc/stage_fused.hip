@@ -4,6 +4,11 @@
 // columns of every refinement level, without ever storing the element-local
 // right-hand side.
 //
+// Two kernels do this.  The owner kernel (stage_own.hip) computes every regular
+// node in one launch, where it applies (own_used below); the column kernel
+// takes everything else: the columns of the irregular nodes, and whole stages
+// with terrain, dissipation or float arithmetic.
+//
 // Column kernel.  A workgroup owns one column and marches up through it in
 // chunks of `layers_per_chunk` stacked elements; one thread per unique node of
 // the chunk, or (split-element order) per element and local node, so that a
@@ -40,6 +45,7 @@
 #include <type_traits>
 
 #include "mesh_build.h"
+#include "nodeval.h"
 #include "sem.h"
 
 namespace sem {
@@ -81,25 +87,6 @@ constexpr int eff_order() {
 template <int NP, int LPC, int ORD>
 constexpr int col_threads() {
     return wg_threads<NP, LPC, ORD == 2>();
-}
-
-// (1+x)^gamma - 1 for the ideal-gas pressure ratio.  For |x| <= 1/64 the
-// Taylor polynomial sum_{n=1..10} C(gamma, n) x^n is used (the first neglected
-// term is below 2^-66 |gamma x|, far under one ulp); otherwise
-// expm1(gamma log1p(x)).  That general branch is kept out of line: inlined,
-// the compiler hoists its polynomial constants out of the chunk loop, where
-// they hold about 30 registers for the whole kernel.
-__device__ __noinline__ double pow1p_minus1_far(double x, double gamma) {
-    return expm1(gamma * log1p(x));
-}
-__device__ __forceinline__ double pow1p_minus1(const DevMesh& m, double x) {
-    if (fabs(x) <= 1.0 / 64.0) {
-        double s = m.binom[10];
-#pragma unroll
-        for (int n = 9; n >= 1; --n) s = s * x + m.binom[n];
-        return s * x;
-    }
-    return pow1p_minus1_far(x, m.gamma);
 }
 
 // At least four waves per SIMD: two workgroups share a CU, so that one can
@@ -1324,7 +1311,7 @@ std::vector<int32_t> colour_units(const HostMesh& H, const std::vector<int32_t>&
 
 }  // namespace
 
-int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P) {
+int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owner) {
     const int np2 = H.np1 * H.np1;
     const bool columns = layout == SEM_LAYOUT_COLUMNS || layout == SEM_LAYOUT_COLUMNS_KZ ||
                          layout == SEM_LAYOUT_COLUMNS_SPLIT;
@@ -1361,6 +1348,135 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P) {
         };
         mark(H.asm_ptr, H.asm_slot, H.n_h);
         mark(H.asmH_ptr, H.asmH_slot, H.n_hh);
+    };
+    auto upv = [&](const auto& v, auto** dst) -> int {
+        void* pd = nullptr;
+        const size_t bytes = v.size() * sizeof(v[0]);
+        // an empty table still gets a (never read) 8-byte allocation
+        int r2 = up(bytes ? static_cast<const void*>(v.data()) : nullptr,
+                    std::max<size_t>(bytes, 8), &pd);
+        *dst = static_cast<std::remove_pointer_t<decltype(dst)>>(pd);
+        return r2;
+    };
+    // Position map, interpolation rows and contribution buffer of a column
+    // launch in which the columns `side_cols` (side_of_col: their index, else
+    // -1) only write their own slots, and the tail that finishes the nodes for
+    // which `in_tail` holds.
+    auto side_tables = [&](const std::vector<int32_t>& side_cols, const std::vector<int32_t>& side_of_col,
+                           const std::vector<char>& done, auto&& in_tail, FusedTables& t, TailTables& T) -> int {
+        int rc;
+        void* d;
+        // positions of side columns become pseudo hanging points n_hh + k (N+1)^2 + pos
+        const int64_t n_pseudo = int64_t(side_cols.size()) * np2;
+        auto pseudo = [&](int32_t slot) {
+            return int32_t(H.n_hh + int64_t(side_of_col[slot / np2]) * np2 + slot % np2);
+        };
+        std::vector<int32_t> gmap_x(H.gmap), hptr_x(H.hang_ptr), hsrc_x(H.hang_src);
+        std::vector<double> hw_x(H.hang_w);
+        std::vector<int32_t> hreal(static_cast<size_t>(H.n_hh + n_pseudo));
+        for (int64_t hh = 0; hh < H.n_hh; ++hh) hreal[hh] = int32_t(H.n_h + hh);
+        if (hptr_x.empty()) hptr_x.push_back(0);
+        for (int32_t sc : side_cols)
+            for (int pos = 0; pos < np2; ++pos) {
+                const int32_t slot = sc * np2 + pos, g = H.gmap[slot];
+                if (g >= 0) {
+                    hsrc_x.push_back(g);
+                    hw_x.push_back(1.0);
+                    hreal[pseudo(slot)] = g;
+                } else {
+                    for (int32_t r = H.hang_ptr[-g - 1]; r < H.hang_ptr[-g]; ++r) {
+                        hsrc_x.push_back(H.hang_src[r]);
+                        hw_x.push_back(H.hang_w[r]);
+                    }
+                    hreal[pseudo(slot)] = int32_t(H.n_h - g - 1);
+                }
+                hptr_x.push_back(int32_t(hsrc_x.size()));
+                gmap_x[slot] = -(pseudo(slot) + 1);
+            }
+        if ((rc = upv(gmap_x, &t.gmap)) != SEM_OK) return rc;
+        if ((rc = upv(hptr_x, &t.hang_ptr)) != SEM_OK) return rc;
+        if ((rc = upv(hsrc_x, &t.hang_src)) != SEM_OK) return rc;
+        if ((rc = upv(hw_x, &t.hang_w)) != SEM_OK) return rc;
+        if ((rc = upv(hreal, &t.hreal)) != SEM_OK) return rc;
+        t.fsh = (H.n_hh + n_pseudo) * H.ldz;
+        if ((rc = up(nullptr, std::max<size_t>(size_t(NF) * t.fsh * 8, 8), &d)) != SEM_OK) return rc;
+        t.cH = static_cast<double*>(d);
+        if (!side_cols.empty()) {
+            // tail tables: unique nodes with side slots or Z^T rows
+            auto is_side = [&](int32_t slot) { return side_of_col[slot / np2] >= 0; };
+            std::vector<int32_t> hT_row(static_cast<size_t>(H.n_h), -1);
+            for (size_t li = 0; li < H.hT_list.size(); ++li) hT_row[H.hT_list[li]] = int32_t(li);
+            std::vector<int32_t> th, tsptr(1, 0), tsslot, thptr(1, 0), thh;
+            std::vector<double> thw;
+            std::vector<uint8_t> tfirst;
+            for (int64_t h = 0; h < H.n_h; ++h) {
+                if (!done.empty() && done[h]) continue;
+                bool any_side = false, any_direct = false;
+                for (int32_t q = H.asm_ptr[h]; q < H.asm_ptr[h + 1]; ++q) {
+                    if (is_side(H.asm_slot[q])) any_side = true;
+                    else any_direct = true;
+                }
+                if (!in_tail(any_side, hT_row[h] >= 0)) continue;
+                th.push_back(int32_t(h));
+                tfirst.push_back(any_direct ? 0 : 1);
+                for (int32_t q = H.asm_ptr[h]; q < H.asm_ptr[h + 1]; ++q)
+                    if (is_side(H.asm_slot[q])) tsslot.push_back(pseudo(H.asm_slot[q]));
+                tsptr.push_back(int32_t(tsslot.size()));
+                if (hT_row[h] >= 0) {
+                    const int32_t li = hT_row[h];
+                    for (int32_t r = H.hT_ptr[li]; r < H.hT_ptr[li + 1]; ++r) {
+                        thh.push_back(H.hT_hh[r]);
+                        thw.push_back(H.hT_w[r]);
+                    }
+                }
+                thptr.push_back(int32_t(thh.size()));
+            }
+            std::vector<int32_t> hsptr(1, 0), hsslot;
+            std::vector<uint8_t> hvalid(static_cast<size_t>(std::max<int64_t>(H.n_hh, 1)), 0);
+            for (int64_t hh = 0; hh < H.n_hh; ++hh) {
+                for (int32_t q = H.asmH_ptr[hh]; q < H.asmH_ptr[hh + 1]; ++q) {
+                    if (is_side(H.asmH_slot[q])) hsslot.push_back(pseudo(H.asmH_slot[q]));
+                    else hvalid[hh] = 1;
+                }
+                hsptr.push_back(int32_t(hsslot.size()));
+            }
+            if (hsptr.size() == 1) hsptr.push_back(0);
+            // one flat list per tail node: its side slots (a group of weight
+            // 1), then per hanging point of its Z^T row a group of weight w:
+            // the point's own contribution (if a column writes it) and its
+            // side slots.  A group sums its rows first and enters the node's
+            // sum times its weight, in the order of Z^T; a group with no row
+            // gets one entry of row -1 (adds nothing).
+            std::vector<int32_t> eptr(1, 0), erow;
+            std::vector<double> ew;
+            std::vector<uint8_t> estart;
+            auto entry = [&](int32_t row, bool start, double w) {
+                erow.push_back(row);
+                estart.push_back(start ? 1 : 0);
+                ew.push_back(w);
+            };
+            for (size_t li = 0; li < th.size(); ++li) {
+                for (int32_t q = tsptr[li]; q < tsptr[li + 1]; ++q) entry(tsslot[q], q == tsptr[li], 1.0);
+                for (int32_t r = thptr[li]; r < thptr[li + 1]; ++r) {
+                    const int32_t hh = thh[r];
+                    bool any = false;
+                    if (hvalid[hh]) { entry(hh, true, thw[r]); any = true; }
+                    for (int32_t q = hsptr[hh]; q < hsptr[hh + 1]; ++q) { entry(hsslot[q], !any, thw[r]); any = true; }
+                    if (!any) entry(-1, true, thw[r]);
+                }
+                eptr.push_back(int32_t(erow.size()));
+            }
+            if ((rc = upv(th, &T.h)) != SEM_OK) return rc;
+            if ((rc = upv(tfirst, &T.first)) != SEM_OK) return rc;
+            if ((rc = upv(eptr, &T.eptr)) != SEM_OK) return rc;
+            if ((rc = upv(erow, &T.erow)) != SEM_OK) return rc;
+            if ((rc = upv(ew, &T.ew)) != SEM_OK) return rc;
+            if ((rc = upv(estart, &T.estart)) != SEM_OK) return rc;
+            T.n = int(th.size());
+            T.fsh = t.fsh;
+            T.cH = t.cH;
+        }
+        return SEM_OK;
     };
     void* d;
     int rc;
@@ -1419,33 +1535,6 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P) {
             cptr.push_back(int32_t(order.size()));
         }
         n_color = int(cptr.size()) - 1;
-        // positions of side columns become pseudo hanging points n_hh + k (N+1)^2 + pos
-        const int64_t n_pseudo = int64_t(side_cols.size()) * np2;
-        auto pseudo = [&](int32_t slot) {
-            return int32_t(H.n_hh + int64_t(side_of_col[slot / np2]) * np2 + slot % np2);
-        };
-        std::vector<int32_t> gmap_x(H.gmap), hptr_x(H.hang_ptr), hsrc_x(H.hang_src);
-        std::vector<double> hw_x(H.hang_w);
-        std::vector<int32_t> hreal(static_cast<size_t>(H.n_hh + n_pseudo));
-        for (int64_t hh = 0; hh < H.n_hh; ++hh) hreal[hh] = int32_t(H.n_h + hh);
-        if (hptr_x.empty()) hptr_x.push_back(0);
-        for (int32_t sc : side_cols)
-            for (int pos = 0; pos < np2; ++pos) {
-                const int32_t slot = sc * np2 + pos, g = H.gmap[slot];
-                if (g >= 0) {
-                    hsrc_x.push_back(g);
-                    hw_x.push_back(1.0);
-                    hreal[pseudo(slot)] = g;
-                } else {
-                    for (int32_t r = H.hang_ptr[-g - 1]; r < H.hang_ptr[-g]; ++r) {
-                        hsrc_x.push_back(H.hang_src[r]);
-                        hw_x.push_back(H.hang_w[r]);
-                    }
-                    hreal[pseudo(slot)] = int32_t(H.n_h - g - 1);
-                }
-                hptr_x.push_back(int32_t(hsrc_x.size()));
-                gmap_x[slot] = -(pseudo(slot) + 1);
-            }
         // first writers among the columns that write nodes themselves; every
         // pseudo point has exactly one writer
         std::vector<int32_t> wcolor(color);
@@ -1456,111 +1545,149 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P) {
         });
         for (int32_t sc : side_cols)
             for (int pos = 0; pos < np2; ++pos) first[size_t(sc) * np2 + pos] = 1;
-        auto upv = [&](const auto& v, auto** dst) -> int {
-            void* pd = nullptr;
-            const size_t bytes = v.size() * sizeof(v[0]);
-            // an empty table still gets a (never read) 8-byte allocation
-            int r2 = up(bytes ? static_cast<const void*>(v.data()) : nullptr,
-                        std::max<size_t>(bytes, 8), &pd);
-            *dst = static_cast<std::remove_pointer_t<decltype(dst)>>(pd);
-            return r2;
-        };
-        if ((rc = upv(gmap_x, &P.t.gmap)) != SEM_OK) return rc;
-        if ((rc = upv(hptr_x, &P.t.hang_ptr)) != SEM_OK) return rc;
-        if ((rc = upv(hsrc_x, &P.t.hang_src)) != SEM_OK) return rc;
-        if ((rc = upv(hw_x, &P.t.hang_w)) != SEM_OK) return rc;
-        if ((rc = upv(hreal, &P.t.hreal)) != SEM_OK) return rc;
-        P.t.fsh = (H.n_hh + n_pseudo) * H.ldz;
-        if (!side_cols.empty()) {
-            // tail tables: unique nodes with side slots or Z^T rows
-            auto is_side = [&](int32_t slot) { return side_of_col[slot / np2] >= 0; };
-            std::vector<int32_t> hT_row(static_cast<size_t>(H.n_h), -1);
-            for (size_t li = 0; li < H.hT_list.size(); ++li) hT_row[H.hT_list[li]] = int32_t(li);
-            std::vector<int32_t> th, tsptr(1, 0), tsslot, thptr(1, 0), thh;
-            std::vector<double> thw;
-            std::vector<uint8_t> tfirst;
-            for (int64_t h = 0; h < H.n_h; ++h) {
-                bool any_side = false, any_direct = false;
-                for (int32_t q = H.asm_ptr[h]; q < H.asm_ptr[h + 1]; ++q) {
-                    if (is_side(H.asm_slot[q])) any_side = true;
-                    else any_direct = true;
-                }
-                if (!any_side && hT_row[h] < 0) continue;
-                th.push_back(int32_t(h));
-                tfirst.push_back(any_direct ? 0 : 1);
-                for (int32_t q = H.asm_ptr[h]; q < H.asm_ptr[h + 1]; ++q)
-                    if (is_side(H.asm_slot[q])) tsslot.push_back(pseudo(H.asm_slot[q]));
-                tsptr.push_back(int32_t(tsslot.size()));
-                if (hT_row[h] >= 0) {
-                    const int32_t li = hT_row[h];
-                    for (int32_t r = H.hT_ptr[li]; r < H.hT_ptr[li + 1]; ++r) {
-                        thh.push_back(H.hT_hh[r]);
-                        thw.push_back(H.hT_w[r]);
-                    }
-                }
-                thptr.push_back(int32_t(thh.size()));
-            }
-            std::vector<int32_t> hsptr(1, 0), hsslot;
-            std::vector<uint8_t> hvalid(static_cast<size_t>(std::max<int64_t>(H.n_hh, 1)), 0);
-            for (int64_t hh = 0; hh < H.n_hh; ++hh) {
-                for (int32_t q = H.asmH_ptr[hh]; q < H.asmH_ptr[hh + 1]; ++q) {
-                    if (is_side(H.asmH_slot[q])) hsslot.push_back(pseudo(H.asmH_slot[q]));
-                    else hvalid[hh] = 1;
-                }
-                hsptr.push_back(int32_t(hsslot.size()));
-            }
-            if (hsptr.size() == 1) hsptr.push_back(0);
-            // one flat list per tail node: its side slots (a group of weight
-            // 1), then per hanging point of its Z^T row a group of weight w:
-            // the point's own contribution (if a column writes it) and its
-            // side slots.  A group sums its rows first and enters the node's
-            // sum times its weight, in the order of Z^T; a group with no row
-            // gets one entry of row -1 (adds nothing).
-            std::vector<int32_t> eptr(1, 0), erow;
-            std::vector<double> ew;
-            std::vector<uint8_t> estart;
-            auto entry = [&](int32_t row, bool start, double w) {
-                erow.push_back(row);
-                estart.push_back(start ? 1 : 0);
-                ew.push_back(w);
-            };
-            for (size_t li = 0; li < th.size(); ++li) {
-                for (int32_t q = tsptr[li]; q < tsptr[li + 1]; ++q) entry(tsslot[q], q == tsptr[li], 1.0);
-                for (int32_t r = thptr[li]; r < thptr[li + 1]; ++r) {
-                    const int32_t hh = thh[r];
-                    bool any = false;
-                    if (hvalid[hh]) { entry(hh, true, thw[r]); any = true; }
-                    for (int32_t q = hsptr[hh]; q < hsptr[hh + 1]; ++q) { entry(hsslot[q], !any, thw[r]); any = true; }
-                    if (!any) entry(-1, true, thw[r]);
-                }
-                eptr.push_back(int32_t(erow.size()));
-            }
-            TailTables& T = P.tail;
-            if ((rc = upv(th, &T.h)) != SEM_OK) return rc;
-            if ((rc = upv(tfirst, &T.first)) != SEM_OK) return rc;
-            if ((rc = upv(eptr, &T.eptr)) != SEM_OK) return rc;
-            if ((rc = upv(erow, &T.erow)) != SEM_OK) return rc;
-            if ((rc = upv(ew, &T.ew)) != SEM_OK) return rc;
-            if ((rc = upv(estart, &T.estart)) != SEM_OK) return rc;
-            T.n = int(th.size());
-            T.fsh = P.t.fsh;
-            P.has_tail = true;
-        }
+        if ((rc = side_tables(side_cols, side_of_col, {},
+                              [](bool any_side, bool hanging_parent) { return any_side || hanging_parent; },
+                              P.t, P.tail)) != SEM_OK)
+            return rc;
+        P.has_tail = !side_cols.empty();
         if ((rc = up(order.data(), order.size() * 4, &d)) != SEM_OK) return rc;
         P.t.col_order = static_cast<const int32_t*>(d);
         if ((rc = up(cptr.data(), cptr.size() * 4, &d)) != SEM_OK) return rc;
         P.t.color_ptr = static_cast<const int32_t*>(d);
         if ((rc = up(first.data(), first.size(), &d)) != SEM_OK) return rc;
         P.t.first = static_cast<const uint8_t*>(d);
-        if ((rc = up(nullptr, size_t(NF) * P.t.fsh * 8, &d)) != SEM_OK) return rc;
-        P.t.cH = static_cast<double*>(d);
-        P.tail.cH = P.t.cH;
         P.t.n_color = n_color;
         P.t.layers_per_chunk = lpc;
         P.t.thread_order = layout == SEM_LAYOUT_COLUMNS_KZ ? 1 : layout == SEM_LAYOUT_COLUMNS_SPLIT ? 2 : 0;
         P.color_ptr_host = cptr;
     }
     P.layout = columns ? layout : SEM_LAYOUT_COLUMNS;
+    if (columns && owner && own_applies(H.N, H.n_col)) {
+        // ---- owner kernel: the regular nodes and their owners.  Nodes inside
+        // a column are regular (a coarse face has none), so that only the
+        // positions on its sides are looked at.
+        const int N = H.N, np1 = H.np1, HS = own_positions(N);
+        // per node the column that has it at (i, j), by whether i and j are N
+        struct At { int32_t col[4]; int32_t n, lev; };
+        constexpr int32_t NONE = -1, MIXED = -2;
+        std::vector<At> at(static_cast<size_t>(H.n_h), At{{NONE, NONE, NONE, NONE}, 0, NONE});
+        std::vector<char> side(static_cast<size_t>(H.n_col), 0), regular(static_cast<size_t>(H.n_h), 1);
+        std::vector<uint64_t> mask(static_cast<size_t>(H.n_col), 0);
+        std::vector<int32_t> sides;
+        uint64_t inside = 0;
+        for (int pos = 0; pos < np2; ++pos) {
+            const int i = pos % np1, j = pos / np1;
+            if (i == 0 || j == 0 || i == N || j == N) sides.push_back(pos);
+            else inside |= uint64_t(1) << (i + N * j);
+        }
+        for (int32_t h : H.hT_list) at[h].lev = MIXED;
+        for (int32_t cc = 0; cc < H.n_col; ++cc)
+            for (int32_t pos : sides) {
+                const int32_t h = H.gmap[size_t(cc) * np2 + pos];
+                if (h < 0) {
+                    side[cc] = 1;
+                    continue;
+                }
+                At& x = at[h];
+                const int k = (pos % np1 == N) + 2 * (pos / np1 == N);
+                x.lev = x.col[k] == NONE && (x.lev == NONE || x.lev == H.col_level[cc]) ? H.col_level[cc] : MIXED;
+                x.col[k] = cc;
+                ++x.n;
+            }
+        for (int32_t cc = 0; cc < H.n_col; ++cc) {
+            mask[cc] = inside;
+            for (int32_t pos : sides) {
+                const int32_t h = H.gmap[size_t(cc) * np2 + pos];
+                if (h < 0) continue;
+                const At& x = at[h];
+                // the owner's position of the node: 0 where it is N here
+                const int i = pos % np1 % N, j = pos / np1 % N;
+                if (x.lev == MIXED || x.n != (i == 0 ? 2 : 1) * (j == 0 ? 2 : 1)) {
+                    side[cc] = 1;
+                    regular[h] = 0;
+                } else if (pos % np1 < N && pos / np1 < N) {
+                    mask[cc] |= uint64_t(1) << (i + N * j);
+                }
+            }
+        }
+        // owners in Morton order of their lower-left corners, so that an
+        // XCD's share of the list is a patch of the mesh
+        std::vector<std::pair<uint64_t, int32_t>> own;
+        std::vector<int32_t> side_cols, side_of_col(static_cast<size_t>(H.n_col), -1);
+        for (int cidx = 0; cidx < H.n_col; ++cidx) {
+            if (mask[cidx]) {
+                const int sh = H.max_level - H.col_level[cidx];
+                const uint64_t x = uint64_t(H.col_ix[cidx]) << sh, y = uint64_t(H.col_iy[cidx]) << sh;
+                uint64_t key = 0;
+                for (int bit = 0; bit < 31; ++bit) key |= ((x >> bit) & 1) << (2 * bit) | ((y >> bit) & 1) << (2 * bit + 1);
+                own.push_back({key, cidx});
+            }
+            if (side[cidx]) {
+                side_of_col[cidx] = int32_t(side_cols.size());
+                side_cols.push_back(cidx);
+            }
+        }
+        std::sort(own.begin(), own.end());
+        std::vector<int32_t> map(own.size() * HS);
+        std::vector<double> sxy;
+        std::vector<uint64_t> omask;
+        std::vector<uint8_t> ohang;
+        int32_t* out = map.data();
+        for (const auto& kc : own) {
+            const int32_t cc = kc.second;
+            int32_t lowest = 0;
+            auto pos = [&](int32_t col, int i, int j) {
+                const int32_t g = H.gmap[size_t(col) * np2 + i + np1 * j];
+                lowest = std::min(lowest, g);
+                *out++ = g;
+            };
+            // the neighbour across the node at position x of the lower left
+            // sides; for a node not computed here: any rows
+            auto across = [&](int x, int k) {
+                const int32_t h = H.gmap[size_t(cc) * np2 + x];
+                return h >= 0 && regular[h] ? at[h].col[k] : cc;
+            };
+            for (int j = 0; j < N; ++j)
+                for (int i = 0; i < N; ++i) pos(cc, i, j);
+            for (int j = 0; j < N; ++j) pos(cc, N, j);
+            for (int i = 0; i < N; ++i) pos(cc, i, N);
+            for (int j = 0; j < N; ++j) {
+                const int32_t left = across(np1 * j, 1);
+                for (int i = 0; i < N; ++i) pos(left, i, j);
+            }
+            for (int i = 0; i < N; ++i) {
+                const int32_t below = across(i, 2);
+                for (int j = 0; j < N; ++j) pos(below, i, j);
+            }
+            sxy.push_back(H.col_sx[cc]);
+            sxy.push_back(H.col_sy[cc]);
+            omask.push_back(mask[cc]);
+            ohang.push_back(lowest < 0 ? 1 : 0);
+        }
+        if ((rc = upv(map, &P.ot.map)) != SEM_OK) return rc;
+        if ((rc = upv(sxy, &P.ot.sxy)) != SEM_OK) return rc;
+        if ((rc = upv(omask, &P.ot.mask)) != SEM_OK) return rc;
+        if ((rc = upv(ohang, &P.ot.hang)) != SEM_OK) return rc;
+        P.ot.n = int(own.size());
+        P.n_side = int(side_cols.size());
+        if (P.n_side > 0) {
+            if ((rc = side_tables(side_cols, side_of_col, regular, [](bool, bool) { return true; }, P.to, P.own_tail)) != SEM_OK)
+                return rc;
+            std::vector<uint8_t> first(H.gmap.size(), 1);   // every slot has one writer
+            if ((rc = upv(first, &P.to.first)) != SEM_OK) return rc;
+            // columns with the most hanging positions first, as above
+            std::vector<int32_t> n_hang(static_cast<size_t>(H.n_col), 0);
+            for (int32_t sc : side_cols)
+                for (int pos = 0; pos < np2; ++pos) n_hang[sc] += H.gmap[size_t(sc) * np2 + pos] < 0;
+            std::stable_sort(side_cols.begin(), side_cols.end(),
+                             [&](int32_t x, int32_t y) { return n_hang[x] > n_hang[y]; });
+            if ((rc = upv(side_cols, &P.to.col_order)) != SEM_OK) return rc;
+            P.to.n_color = 1;
+            P.to.layers_per_chunk = lpc;
+            P.to.thread_order = P.t.thread_order;
+        }
+        P.own = true;
+    }
     if (columns) return SEM_OK;
 
     // ---- block layout: units are the 2 x 2 blocks and the columns in no block
@@ -1702,6 +1829,30 @@ bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& P, int prec) {
     return (m.cs > 0.0 || m.sponge) && !m.zs && prec == SEM_FP64 && P.layout != SEM_LAYOUT_BLOCKS;
 }
 
+// The owner kernel takes over where it has an instance (N >= 2).  us per stage,
+// column kernel at its best chunk and owner kernel, by N:
+//   N  elements        col  own     elements       col  own
+//   2  24 x 24 x 16     31   13     64 x 64 x 16    54   38
+//   3  7 x 6 x 5        35    9     64 x 64 x 16   134   97
+//   4  8 x 8 x 4        27   12     64 x 64 x 16   230  172
+//   5  37 x 29 x 5      86   75     48 x 48 x 16   394  281
+//   6  20 x 20 x 6      81   49     40 x 40 x 12   317  317
+//   7  10 x 10 x 8     144   43     40 x 40 x 12   479  490
+//   8  12 x 12 x 8     204   62     36 x 36 x 8    465  379
+// At N = 7 the state of more columns than the L2s hold at once is read more
+// than once (rows of odd length: a line has parts of two chunks), and the rule
+// draws the line at three columns per CU: 24 x 24 x 8 160 against 129, 28 x 28
+// x 8 180 against 177, 64 x 64 x 8 and a level 960 against 1035.  Left to the
+// column kernel: terrain and dissipation (their terms need more of a neighbour
+// than one line) and float (p' is rounded to float, and which way it goes must
+// not depend on the order of the sums: 8e-8 of the rms in w after one step).
+bool own_applies(int N, int n_col) { return own_supported(N) && (N != 7 || n_col <= 768); }
+
+bool own_used(const DevMesh& m, int prec) {
+    return prec == SEM_FP64 && own_applies(m.N, m.n_col) && own_fits(m) && !m.zs && !m.rx && m.cs == 0.0 &&
+           !m.sponge;
+}
+
 int fused_stage_launch(const DevMesh& m_in, const FusedPlan& P, double a, double b, double c,
                        const double* qn, const double* qs, double* qo, int prec, hipStream_t s) {
     const bool f32 = prec == SEM_FP32;
@@ -1730,6 +1881,24 @@ int fused_stage_launch(const DevMesh& m_in, const FusedPlan& P, double a, double
                 if (rc != SEM_OK) return rc;
             }
         }
+    } else if (P.own && own_used(m, prec)) {
+        // the irregular nodes' columns write their slots, the owner kernel
+        // finishes the regular nodes, the tail the irregular ones
+        if (P.n_side > 0) {
+            const int rc = launch_t<double, false>(m, P.to, 0, P.n_side, a, b, c, qn, qs, qo, s);
+            if (rc != SEM_OK) return rc;
+        }
+        const int rc = own_launch(m, P.ot, a, b, c, qn, qs, qo, s);
+        if (rc != SEM_OK) return rc;
+        if (P.n_side > 0) {
+            const int64_t n2 = int64_t(P.own_tail.n) * m.nzn;
+            if (n2 > 0) {
+                const int64_t g = std::min<int64_t>((n2 + 255) / 256, 65536);
+                hipLaunchKernelGGL(k_stage_tail, dim3(unsigned(g)), dim3(256), 0, s, m, P.own_tail, a, b, c, qn, qs, qo);
+                if (hipGetLastError() != hipSuccess) return SEM_ERR_HIP;
+            }
+        }
+        return SEM_OK;
     } else {
         const FusedTables& t = P.t;
         for (int k = 0; k < t.n_color; ++k) {
