@@ -94,10 +94,13 @@ struct sem_transfer {
     int32_t* ptr = nullptr;
     int32_t* src = nullptr;
     double* w = nullptr;
+    int n_long = 0;                 // rows that a workgroup sums (longest first)
+    int32_t* long_rows = nullptr;
     ~sem_transfer() {
         if (ptr) (void)hipFree(ptr);
         if (src) (void)hipFree(src);
         if (w) (void)hipFree(w);
+        if (long_rows) (void)hipFree(long_rows);
     }
 };
 
