@@ -41,6 +41,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cstring>
 #include <string>
 #include <type_traits>
 
@@ -1309,9 +1310,56 @@ std::vector<int32_t> colour_units(const HostMesh& H, const std::vector<int32_t>&
     return color;
 }
 
-}  // namespace
+// bit b of x at bit 2b
+uint64_t spread_bits(uint64_t x) {
+    x &= 0xffffffffu;
+    x = (x | x << 16) & 0x0000ffff0000ffffu;
+    x = (x | x << 8) & 0x00ff00ff00ff00ffu;
+    x = (x | x << 4) & 0x0f0f0f0f0f0f0f0fu;
+    x = (x | x << 2) & 0x3333333333333333u;
+    return (x | x << 1) & 0x5555555555555555u;
+}
 
-int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owner) {
+// The plan's tables in a few allocations, each filled by one copy: some 40
+// small ones take as long as building them (two-level mesh over 64 x 64
+// columns at N = 4: 4.4 ms for the tables of a layout, 3.1 so).
+struct Arena {
+    static constexpr size_t CHUNK = size_t(2) << 20;
+    FusedPlan& P;
+    std::vector<char> host;
+    char* dev = nullptr;
+    size_t cap = 0;
+    explicit Arena(FusedPlan& plan) : P(plan) {}
+    int flush() {
+        const bool ok = host.empty() || hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice) == hipSuccess;
+        host.clear();
+        return ok ? SEM_OK : SEM_ERR_HIP;
+    }
+    int alloc(size_t bytes, void** dst) {
+        if (hipMalloc(dst, bytes) != hipSuccess) return SEM_ERR_HIP;
+        P.allocs.push_back(*dst);
+        P.bytes += int64_t(bytes);
+        return SEM_OK;
+    }
+    // device address of a table (null if empty); its contents are there after flush()
+    int put(const void* src, size_t bytes, void** dst) {
+        const size_t at = (host.size() + 255) / 256 * 256;
+        if (!dev || at + bytes > cap) {
+            if (const int rc = flush(); rc != SEM_OK) return rc;
+            void* d = nullptr;
+            cap = std::max(bytes, CHUNK);
+            if (const int rc = alloc(cap, &d); rc != SEM_OK) return rc;
+            dev = static_cast<char*>(d);
+        }
+        const size_t o = host.empty() ? 0 : at;
+        host.resize(o + bytes);
+        std::memcpy(host.data() + o, src, bytes);
+        *dst = dev + o;
+        return SEM_OK;
+    }
+};
+
+int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owner, Arena& A) {
     const int np2 = H.np1 * H.np1;
     const bool columns = layout == SEM_LAYOUT_COLUMNS || layout == SEM_LAYOUT_COLUMNS_KZ ||
                          layout == SEM_LAYOUT_COLUMNS_SPLIT;
@@ -1328,11 +1376,7 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, boo
     auto up = [&](const void* src, size_t bytes, void** dst) -> int {
         *dst = nullptr;
         if (bytes == 0) return SEM_OK;
-        if (hipMalloc(dst, bytes) != hipSuccess) return SEM_ERR_HIP;
-        P.allocs.push_back(*dst);
-        P.bytes += int64_t(bytes);
-        if (src && hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess) return SEM_ERR_HIP;
-        return SEM_OK;
+        return src ? A.put(src, bytes, dst) : A.alloc(bytes, dst);
     };
     // first contributor of every node: the lowest colour among its units
     auto mark_first = [&](const std::vector<int32_t>& unit_of_col, const std::vector<int32_t>& color,
@@ -1365,7 +1409,6 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, boo
     auto side_tables = [&](const std::vector<int32_t>& side_cols, const std::vector<int32_t>& side_of_col,
                            const std::vector<char>& done, auto&& in_tail, FusedTables& t, TailTables& T) -> int {
         int rc;
-        void* d;
         // positions of side columns become pseudo hanging points n_hh + k (N+1)^2 + pos
         const int64_t n_pseudo = int64_t(side_cols.size()) * np2;
         auto pseudo = [&](int32_t slot) {
@@ -1399,8 +1442,6 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, boo
         if ((rc = upv(hw_x, &t.hang_w)) != SEM_OK) return rc;
         if ((rc = upv(hreal, &t.hreal)) != SEM_OK) return rc;
         t.fsh = (H.n_hh + n_pseudo) * H.ldz;
-        if ((rc = up(nullptr, std::max<size_t>(size_t(NF) * t.fsh * 8, 8), &d)) != SEM_OK) return rc;
-        t.cH = static_cast<double*>(d);
         if (!side_cols.empty()) {
             // tail tables: unique nodes with side slots or Z^T rows
             auto is_side = [&](int32_t slot) { return side_of_col[slot / np2] >= 0; };
@@ -1474,7 +1515,6 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, boo
             if ((rc = upv(estart, &T.estart)) != SEM_OK) return rc;
             T.n = int(th.size());
             T.fsh = t.fsh;
-            T.cH = t.cH;
         }
         return SEM_OK;
     };
@@ -1618,8 +1658,7 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, boo
             if (mask[cidx]) {
                 const int sh = H.max_level - H.col_level[cidx];
                 const uint64_t x = uint64_t(H.col_ix[cidx]) << sh, y = uint64_t(H.col_iy[cidx]) << sh;
-                uint64_t key = 0;
-                for (int bit = 0; bit < 31; ++bit) key |= ((x >> bit) & 1) << (2 * bit) | ((y >> bit) & 1) << (2 * bit + 1);
+                const uint64_t key = spread_bits(x) | spread_bits(y) << 1;
                 own.push_back({key, cidx});
             }
             if (side[cidx]) {
@@ -1688,6 +1727,11 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, boo
         }
         P.own = true;
     }
+    // one buffer of contributions: a stage runs the coloured launches or the
+    // owner kernel's, and stages of one handle do not overlap
+    if ((rc = up(nullptr, std::max<size_t>(size_t(NF) * std::max(P.t.fsh, P.to.fsh) * 8, 8), &d)) != SEM_OK) return rc;
+    P.t.cH = P.to.cH = static_cast<double*>(d);
+    P.tail.cH = P.own_tail.cH = P.t.cH;
     if (columns) return SEM_OK;
 
     // ---- block layout: units are the 2 x 2 blocks and the columns in no block
@@ -1799,6 +1843,14 @@ int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, boo
     P.n_unit_color = n_color;
     P.layout = SEM_LAYOUT_BLOCKS;
     return SEM_OK;
+}
+
+}  // namespace
+
+int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owner) {
+    Arena A(P);
+    const int rc = plan_build(H, layout, param, P, owner, A);
+    return rc != SEM_OK ? rc : A.flush();
 }
 
 void fused_plan_free(FusedPlan& P) {
