@@ -22,22 +22,17 @@ namespace {
 struct Scale16 { float v[SEM_NFEAT]; };
 struct ThrF { double v[SEM_MAX_LEVEL]; };
 
-// accumulators of the element pass: 13 maxima and one sum
+// accumulators of the element pass: 13 maxima (of squares where a square root
+// is taken: it keeps their order) and one sum
 enum { A_ZABS, A_UH, A_W, A_TMAX, A_TMIN, A_GP, A_GT, A_DIV, A_RMAX, A_RMIN, A_UHP, A_ZABSP,
        A_CRIT, A_NMAX, A_ZSUM = A_NMAX, A_N };
 
-__device__ __forceinline__ double wave_max(double x) {
-    for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
-    return x;
-}
-__device__ __forceinline__ double wave_sum(double x) {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
+// square root of a maximum of squares (-infinity: of no number)
+__device__ __forceinline__ double root(double x) { return x >= 0.0 ? sqrt(x) : x; }
 
 }  // namespace
 
-// One workgroup per element, one thread per local node.  Raw features:
+// Raw features of an element (element pass of nodeval.h):
 //  0 level, 1 max|zeta|, 2 mean zeta, 3 max|u_h|, 4 max|w|, 5 max theta',
 //  6 min theta', 7 max|grad p'|, 8 max|grad theta'|, 9 max|div u|,
 //  10 rho' range, 11-12 (neighbour pass), 13 change of max|u_h| and
@@ -48,144 +43,201 @@ __device__ __forceinline__ double wave_sum(double x) {
 // a_x d/dzf, d/dy likewise, d/dz = g_s d/dzf, and p' from the per-node
 // reference).  dem = number of thresholds the criterion's element maximum
 // exceeds (the level the criterion asks for).
+//
+// 6,220 columns of 8 layers at N = 4 (three levels): 142 us, 0.28 GB read; 320
+// with a workgroup per element and a thread per node, whose 14 results took a
+// wave reduction each.  What is left is latency at ten waves per CU (LDS), half
+// of it the wait for the nodes; VALU issue is 40 %.
 template <int NP>
-__global__ void __launch_bounds__(((NP * NP * NP + 63) / 64) * 64)
+__global__ void __launch_bounds__(pass_threads<NP>(), NP <= 5 ? 3 : 2)
 k_features(DevMesh m, const double* __restrict__ q, const double* __restrict__ qp,
            const int8_t* __restrict__ plain, int criterion, ThrF thr, int lvl_max, Scale16 sc,
            float* __restrict__ feat, double* __restrict__ aux, int8_t* __restrict__ dem) {
     constexpr int NP2 = NP * NP, NP3 = NP2 * NP, N = NP - 1;
-    constexpr int NW = (NP3 + 63) / 64;
-    __shared__ double su[NP3], sv[NP3], sw[NP3], st[NP3], spp[NP3], sup[NP3], svp[NP3];
-    __shared__ double red[NW][A_N];
-    __shared__ double s_zs[NP2];          // terrain: surface height per position
-    const int e = blockIdx.x;
-    const int c = e / m.n_z, layer = e - c * m.n_z;
-    const int t = threadIdx.x;
-    const bool act = t < NP3;
-    const int i = t % NP, j = (t / NP) % NP, k = t / NP2;
-    const int kz = layer * N + k;
+    constexpr int PT = pass_threads<NP>(), ST = pass_stride<NP>(), TN = NP2 * ST, LZ = pass_layers<NP>();
+    constexpr int RED = A_N * (PT + 1);
+    // the tiles, then (after them) the threads' maxima
+    __shared__ double2 buf[4 * TN > (RED + 1) / 2 ? 4 * TN : (RED + 1) / 2];
+    __shared__ double sD[NP2], s_zs[NP2];     // s_zs, terrain: surface height per position
+    __shared__ double s_max[LZ][A_N];
+    double2 *t_uv = buf, *t_pt = buf + TN, *t_prev = buf + 2 * TN, *t_wr = buf + 3 * TN;
+    double* red = reinterpret_cast<double*>(buf);
+    const PassItem it = pass_item<NP>(m);
+    const int c = it.c, nk = it.layers * N + 1, z0 = it.layer0 * N, tid = threadIdx.x;
     const bool ter = m.zs != nullptr;
-    if (ter && t < NP2) {
-        const int gz = m.gmap[c * NP2 + t];
-        s_zs[t] = m.zs[gz >= 0 ? gz : m.n_h - gz - 1];
-    }
-    double rp = 0, u = 0, v = 0, w = 0, tp = 0, up = 0, vp = 0;
-    if (act) {
-        const int g = m.gmap[c * NP2 + i + NP * j];
-        rp = node_value(m, q, g, 0, kz);
-        u = node_value(m, q, g, 1, kz);
-        v = node_value(m, q, g, 2, kz);
-        w = node_value(m, q, g, 3, kz);
-        tp = node_value(m, q, g, 4, kz);
-        up = node_value(m, qp, g, 1, kz);
-        vp = node_value(m, qp, g, 2, kz);
-        su[t] = u; sv[t] = v; sw[t] = w; st[t] = tp; sup[t] = up; svp[t] = vp;
-        // p' = p0 ((1 + rho'/rho0)(1 + theta'/theta0))^gamma - p0 without cancellation
+    for (int x = tid; x < NP2; x += PT) {
+        sD[x] = m.D[x];
         if (ter) {
-            // per-node reference (hanging rows: the coarse face's interpolant)
-            const int64_t fsr = int64_t(m.n_h + m.n_hh) * m.ldz;
-            const int64_t o = int64_t(g >= 0 ? g : m.n_h - g - 1) * m.ldz + kz;
-            spp[t] = m.ref_n[3 * fsr + o] *
-                     expm1(m.gamma * (log1p(rp * m.ref_n[fsr + o]) + log1p(tp * m.ref_n[2 * fsr + o])));
-        } else {
-            spp[t] = m.p0[kz] * expm1(m.gamma * (log1p(rp / m.rho0[kz]) + log1p(tp / m.theta0[kz])));
+            const int gz = m.gmap[c * NP2 + x];
+            s_zs[x] = m.zs[gz >= 0 ? gz : m.n_h - gz - 1];
+        }
+    }
+    // (a few nodes' loads at once; hanging positions then replace theirs)
+    constexpr int U = 4;
+    const int64_t fs = int64_t(m.n_h) * m.ldz;
+    for (int x0 = tid; x0 < NP2 * nk; x0 += U * PT) {
+        int g[U], o[U], kz[U];
+        double a[U][SEM_NFIELDS], b[U][2];
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            const int x = min(x0 + s * PT, NP2 * nk - 1), pos = x / nk, kl = x - pos * nk;
+            g[s] = m.gmap[c * NP2 + pos];
+            o[s] = pos * ST + kl;
+            kz[s] = z0 + kl;
+        }
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            const int64_t r = int64_t(max(g[s], 0)) * m.ldz + kz[s];
+#pragma unroll
+            for (int f = 0; f < SEM_NFIELDS; ++f) a[s][f] = q[f * fs + r];
+            b[s][0] = qp[fs + r];
+            b[s][1] = qp[2 * fs + r];
+        }
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            if (x0 + s * PT >= NP2 * nk) break;
+            if (g[s] < 0) {
+                node_values<0, SEM_NFIELDS>(m, q, g[s], kz[s], a[s]);
+                node_values<1, 2>(m, qp, g[s], kz[s], b[s]);
+            }
+            // p' = p0 ((1 + rho'/rho0)(1 + theta'/theta0))^gamma - p0 without cancellation
+            double p0, ra, tb;
+            if (ter) {
+                // per-node reference (hanging rows: the coarse face's interpolant)
+                const int64_t fsr = int64_t(m.n_h + m.n_hh) * m.ldz;
+                const int64_t r = int64_t(g[s] >= 0 ? g[s] : m.n_h - g[s] - 1) * m.ldz + kz[s];
+                ra = a[s][0] * m.ref_n[fsr + r];
+                tb = a[s][4] * m.ref_n[2 * fsr + r];
+                p0 = m.ref_n[3 * fsr + r];
+            } else {
+                ra = a[s][0] * m.inv_rho0[kz[s]];
+                tb = a[s][4] * m.inv_theta0[kz[s]];
+                p0 = m.p0[kz[s]];
+            }
+            t_uv[o[s]] = double2{a[s][1], a[s][2]};
+            t_pt[o[s]] = double2{p0 * pow1p_minus1(m, ra + tb + ra * tb), a[s][4]};
+            t_prev[o[s]] = double2{b[s][0], b[s][1]};
+            t_wr[o[s]] = double2{a[s][3], a[s][0]};
         }
     }
     __syncthreads();
-    double a[A_N];
+    double acc[A_N];
 #pragma unroll
-    for (int r = 0; r < A_N; ++r) a[r] = -INFINITY;
-    a[A_ZSUM] = 0.0;
-    if (act) {
-        const double sx = 2.0 / m.col_dx[c], sy = 2.0 / m.col_dy[c], szz = 2.0 / m.dz[layer];
-        double vx = 0, uy = 0, ux = 0, vy = 0, wz = 0, px = 0, py = 0, pz = 0, tx = 0, ty = 0,
-               tz = 0, vpx = 0, upy = 0;
-        for (int mm = 0; mm < NP; ++mm) {
-            const double dxm = m.D[i * NP + mm], dym = m.D[j * NP + mm], dzm = m.D[k * NP + mm];
-            const int ox = mm + NP * (j + NP * k), oy = i + NP * (mm + NP * k), oz = i + NP * (j + NP * mm);
-            vx += dxm * sv[ox]; ux += dxm * su[ox]; px += dxm * spp[ox]; tx += dxm * st[ox];
-            vpx += dxm * svp[ox];
-            uy += dym * su[oy]; vy += dym * sv[oy]; py += dym * spp[oy]; ty += dym * st[oy];
-            upy += dym * sup[oy];
-            wz += dzm * sw[oz]; pz += dzm * spp[oz]; tz += dzm * st[oz];
-        }
-        vx *= sx; ux *= sx; px *= sx; tx *= sx; vpx *= sx;
-        uy *= sy; vy *= sy; py *= sy; ty *= sy; upy *= sy;
-        wz *= szz; pz *= szz; tz *= szz;
+    for (int r = 0; r < A_N; ++r) acc[r] = -INFINITY;
+    acc[A_ZSUM] = 0.0;
+    const int lay = tid / NP2, p = tid - lay * NP2;
+    if (lay < it.layers) {
+        const int i = p % NP, j = p / NP;
+        const double sx = 2.0 / m.col_dx[c], sy = 2.0 / m.col_dy[c], szz = 2.0 / m.dz[it.layer0 + lay];
+        double zx = 0, zy = 0, gs = 1.0;
         if (ter) {
             // terrain-following mapping: g_s = 1/(1 - zs/(H - z0)),
             // a_x = -g_s (H - zf)/(H - z0) dzs/dx, a_y likewise
-            double uz = 0, vz = 0, upz = 0, vpz = 0, zx = 0, zy = 0;
             for (int mm = 0; mm < NP; ++mm) {
-                const double dzm = m.D[k * NP + mm];
-                const int oz = i + NP * (j + NP * mm);
-                uz += dzm * su[oz]; vz += dzm * sv[oz]; upz += dzm * sup[oz]; vpz += dzm * svp[oz];
-                zx += m.D[i * NP + mm] * s_zs[mm + NP * j];
-                zy += m.D[j * NP + mm] * s_zs[i + NP * mm];
+                zx += sD[i * NP + mm] * s_zs[mm + NP * j];
+                zy += sD[j * NP + mm] * s_zs[i + NP * mm];
             }
-            uz *= szz; vz *= szz; upz *= szz; vpz *= szz;
-            const double gs = 1.0 / (1.0 - s_zs[i + NP * j] * m.inv_depth);
-            const double tg = m.tfac[kz] * gs;
-            const double ax = -tg * zx * sx, ay = -tg * zy * sy;
-            vx += ax * vz; ux += ax * uz; px += ax * pz; tx += ax * tz; vpx += ax * vpz;
-            uy += ay * uz; vy += ay * vz; py += ay * pz; ty += ay * tz; upy += ay * upz;
-            wz *= gs; pz *= gs; tz *= gs;
+            gs = 1.0 / (1.0 - s_zs[p] * m.inv_depth);
         }
-        const double zeta = vx - uy, zetap = vpx - upy;
-        a[A_ZABS] = fabs(zeta);
-        a[A_ZSUM] = zeta;
-        a[A_UH] = sqrt(u * u + v * v);
-        a[A_W] = fabs(w);
-        a[A_TMAX] = tp;
-        a[A_TMIN] = -tp;
-        a[A_GP] = sqrt(px * px + py * py + pz * pz);
-        a[A_GT] = sqrt(tx * tx + ty * ty + tz * tz);
-        a[A_DIV] = fabs(ux + vy + wz);
-        a[A_RMAX] = rp;
-        a[A_RMIN] = -rp;
-        a[A_UHP] = sqrt(up * up + vp * vp);
-        a[A_ZABSP] = fabs(zetap);
-        a[A_CRIT] = (criterion == SEM_CRIT_SPEED) ? sqrt(u * u + v * v + w * w) : zeta;
+#pragma unroll 1
+        for (int k = 0; k < NP; ++k) {
+            const int kl = lay * N + k;
+            double vx = 0, uy = 0, ux = 0, vy = 0, wz = 0, px = 0, py = 0, pz = 0, tx = 0, ty = 0,
+                   tz = 0, vpx = 0, upy = 0;
+#pragma unroll
+            for (int mm = 0; mm < NP; ++mm) {
+                const double dxm = sD[i * NP + mm], dym = sD[j * NP + mm], dzm = m.D[k * NP + mm];
+                const int ox = (mm + NP * j) * ST + kl, oy = (i + NP * mm) * ST + kl, oz = p * ST + lay * N + mm;
+                const double2 xu = t_uv[ox], xp = t_pt[ox], yu = t_uv[oy], yp = t_pt[oy], zp = t_pt[oz];
+                vx += dxm * xu.y; ux += dxm * xu.x; px += dxm * xp.x; tx += dxm * xp.y;
+                vpx += dxm * t_prev[ox].y;
+                uy += dym * yu.x; vy += dym * yu.y; py += dym * yp.x; ty += dym * yp.y;
+                upy += dym * t_prev[oy].x;
+                wz += dzm * t_wr[oz].x; pz += dzm * zp.x; tz += dzm * zp.y;
+            }
+            vx *= sx; ux *= sx; px *= sx; tx *= sx; vpx *= sx;
+            uy *= sy; vy *= sy; py *= sy; ty *= sy; upy *= sy;
+            wz *= szz; pz *= szz; tz *= szz;
+            if (ter) {
+                double uz = 0, vz = 0, upz = 0, vpz = 0;
+                for (int mm = 0; mm < NP; ++mm) {
+                    const double dzm = m.D[k * NP + mm];
+                    const int oz = p * ST + lay * N + mm;
+                    uz += dzm * t_uv[oz].x; vz += dzm * t_uv[oz].y;
+                    upz += dzm * t_prev[oz].x; vpz += dzm * t_prev[oz].y;
+                }
+                uz *= szz; vz *= szz; upz *= szz; vpz *= szz;
+                const double tg = m.tfac[z0 + kl] * gs;
+                const double ax = -tg * zx * sx, ay = -tg * zy * sy;
+                vx += ax * vz; ux += ax * uz; px += ax * pz; tx += ax * tz; vpx += ax * vpz;
+                uy += ay * uz; vy += ay * vz; py += ay * pz; ty += ay * tz; upy += ay * upz;
+                wz *= gs; pz *= gs; tz *= gs;
+            }
+            const int o = p * ST + kl;
+            const double2 uv = t_uv[o], wr = t_wr[o], prev = t_prev[o];
+            const double u = uv.x, v = uv.y, w = wr.x, rp = wr.y, tp = t_pt[o].y;
+            const double zeta = vx - uy, zetap = vpx - upy;
+            auto top = [&](int r, double x) { acc[r] = fmax(acc[r], x); };
+            top(A_ZABS, fabs(zeta));
+            acc[A_ZSUM] += zeta;
+            top(A_UH, u * u + v * v);
+            top(A_W, fabs(w));
+            top(A_TMAX, tp);
+            top(A_TMIN, -tp);
+            top(A_GP, px * px + py * py + pz * pz);
+            top(A_GT, tx * tx + ty * ty + tz * tz);
+            top(A_DIV, fabs(ux + vy + wz));
+            top(A_RMAX, rp);
+            top(A_RMIN, -rp);
+            top(A_UHP, prev.x * prev.x + prev.y * prev.y);
+            top(A_ZABSP, fabs(zetap));
+            top(A_CRIT, criterion == SEM_CRIT_SPEED ? u * u + v * v + w * w : zeta);
+        }
     }
-#pragma unroll
-    for (int r = 0; r < A_NMAX; ++r) a[r] = wave_max(a[r]);
-    a[A_ZSUM] = wave_sum(a[A_ZSUM]);
-    if ((t & 63) == 0)
-#pragma unroll
-        for (int r = 0; r < A_N; ++r) red[t >> 6][r] = a[r];
     __syncthreads();
-    if (t == 0) {
-        double b[A_N];
-        for (int r = 0; r < A_N; ++r) b[r] = red[0][r];
-        for (int q2 = 1; q2 < NW; ++q2) {
-            for (int r = 0; r < A_NMAX; ++r) b[r] = fmax(b[r], red[q2][r]);
-            b[A_ZSUM] += red[q2][A_ZSUM];
+#pragma unroll
+    for (int r = 0; r < A_N; ++r) red[r * (PT + 1) + tid] = acc[r];
+    __syncthreads();
+    for (int x = tid; x < it.layers * A_N; x += PT) {
+        const int l = x / A_N, r = x - l * A_N;
+        const double* y = red + r * (PT + 1) + l * NP2;
+        double s = y[0];
+        for (int n = 1; n < NP2; ++n) s = r == A_ZSUM ? s + y[n] : fmax(s, y[n]);
+        const bool squares = r == A_UH || r == A_GP || r == A_GT || r == A_UHP ||
+                             (r == A_CRIT && criterion == SEM_CRIT_SPEED);
+        s_max[l][r] = squares ? root(s) : s;
+    }
+    __syncthreads();
+    for (int x = tid; x < it.layers * SEM_NFEAT; x += PT) {
+        const int l = x / SEM_NFEAT, r = x - l * SEM_NFEAT;
+        const double* b = s_max[l];
+        const int64_t e = int64_t(c) * m.n_z + it.layer0 + l;
+        double f = 0.0;
+        switch (r) {
+            case 0: f = m.col_level[c]; break;
+            case 1: f = b[A_ZABS]; break;
+            case 2: f = b[A_ZSUM] / NP3; break;
+            case 3: f = b[A_UH]; break;
+            case 4: f = b[A_W]; break;
+            case 5: f = b[A_TMAX]; break;
+            case 6: f = -b[A_TMIN]; break;
+            case 7: f = b[A_GP]; break;
+            case 8: f = b[A_GT]; break;
+            case 9: f = b[A_DIV]; break;
+            case 10: f = b[A_RMAX] + b[A_RMIN]; break;
+            case 13: f = b[A_UH] - b[A_UHP]; break;
+            case 14: f = b[A_ZABS] - b[A_ZABSP]; break;
+            case 15: f = plain[e]; break;
+            default: break;
         }
-        const int lv = m.col_level[c];
-        double f[SEM_NFEAT];
-        f[0] = lv;
-        f[1] = b[A_ZABS];
-        f[2] = b[A_ZSUM] / NP3;
-        f[3] = b[A_UH];
-        f[4] = b[A_W];
-        f[5] = b[A_TMAX];
-        f[6] = -b[A_TMIN];
-        f[7] = b[A_GP];
-        f[8] = b[A_GT];
-        f[9] = b[A_DIV];
-        f[10] = b[A_RMAX] + b[A_RMIN];
-        f[11] = 0.0;
-        f[12] = 0.0;
-        f[13] = b[A_UH] - b[A_UHP];
-        f[14] = b[A_ZABS] - b[A_ZABSP];
-        f[15] = plain[e];
-        for (int r = 0; r < SEM_NFEAT; ++r) feat[int64_t(e) * SEM_NFEAT + r] = float(f[r] * double(sc.v[r]));
-        aux[2 * int64_t(e)] = b[A_ZABS];
-        aux[2 * int64_t(e) + 1] = b[A_UH];
-        int d = 0;
-        for (int l = 1; l <= lvl_max; ++l)
-            if (b[A_CRIT] > thr.v[l - 1]) d = l;
-        dem[e] = int8_t(d);
+        feat[e * SEM_NFEAT + r] = float(f * double(sc.v[r]));
+        if (r < 2) aux[2 * e + r] = r == 0 ? b[A_ZABS] : b[A_UH];
+        if (r == 2) {
+            int d = 0;
+            for (int lv = 1; lv <= lvl_max; ++lv)
+                if (b[A_CRIT] > thr.v[lv - 1]) d = lv;
+            dem[e] = int8_t(d);
+        }
     }
 }
 
@@ -236,30 +288,43 @@ __global__ void k_forecast_col(DevMesh m, const int8_t* __restrict__ ae, int8_t*
 }
 
 // maximum horizontal wind sqrt(u^2 + v^2) over the unique nodes whose
-// horizontal position lies in [x0, x1] x [y0, y1]: per-block maxima, then one
-// block over the partial results (a maximum does not depend on order)
-constexpr int WIND_BLOCKS = 256;
+// horizontal position lies in [x0, x1] x [y0, y1]: per-block maxima of the
+// squares, then one block over the partial results (a maximum does not depend
+// on order, and the root keeps it).  A thread per row and pair of levels in
+// turn; bound by memory.
+// 100,000 rows of 33 levels: 14 us; 44 with a thread per node, a division by
+// the row length and a root each.
+constexpr int WIND_BLOCKS = 256, WIND_THREADS = 1024;
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(WIND_THREADS)
 k_max_wind(DevMesh m, const double* __restrict__ q, const double* __restrict__ hxy, double x0,
            double x1, double y0, double y1, double* __restrict__ part) {
-    __shared__ double red[4];
-    const int64_t n = int64_t(m.n_h) * m.nzn;
+    using vec = double __attribute__((ext_vector_type(2), aligned(8)));
+    __shared__ double red[WIND_THREADS / 64];
     const int64_t fs = int64_t(m.n_h) * m.ldz;
+    const unsigned L = unsigned(m.nzn + 1) / 2;       // threads of a row
+    const int64_t n = int64_t(m.n_h) * L;
     double best = 0.0;
-    for (int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; t < n;
-         t += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t h = t / m.nzn;
-        const int kz = int(t - h * m.nzn);
-        const double x = hxy[2 * h], y = hxy[2 * h + 1];
-        if (x < x0 || x > x1 || y < y0 || y > y1) continue;
-        const double u = q[fs + h * m.ldz + kz], v = q[2 * fs + h * m.ldz + kz];
-        best = fmax(best, sqrt(u * u + v * v));
+    for (int64_t b = int64_t(blockIdx.x) * WIND_THREADS; b < n; b += int64_t(WIND_BLOCKS) * WIND_THREADS) {
+        const int64_t first = b / L;
+        const unsigned x = unsigned(b - first * L) + threadIdx.x, dh = x / L;
+        const int64_t h = first + dh;
+        if (h >= m.n_h) break;
+        const int k = int(x - dh * L) * 2;
+        const double px = hxy[2 * h], py = hxy[2 * h + 1];
+        if (px < x0 || px > x1 || py < y0 || py > y1) continue;
+        const vec u = *reinterpret_cast<const vec*>(q + fs + h * m.ldz + k);
+        const vec v = *reinterpret_cast<const vec*>(q + 2 * fs + h * m.ldz + k);
+        best = fmax(best, u.x * u.x + v.x * v.x);
+        if (k + 1 < m.nzn) best = fmax(best, u.y * u.y + v.y * v.y);
     }
     for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
     __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < WIND_THREADS / 64; ++w) best = fmax(best, red[w]);
+        part[blockIdx.x] = best;
+    }
 }
 
 __global__ void __launch_bounds__(256)
@@ -270,7 +335,7 @@ k_max_wind_final(const double* __restrict__ part, int n, double* __restrict__ ou
     for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
     __syncthreads();
-    if (threadIdx.x == 0) *out = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    if (threadIdx.x == 0) *out = sqrt(fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
 }
 
 }  // namespace sem
@@ -308,8 +373,8 @@ static int amr_features_impl(const sem_mesh* M, const double* q, const double* q
     switch (d.N) {
 #define CASE(NN)                                                                              \
     case NN:                                                                                  \
-        hipLaunchKernelGGL((sem::k_features<NN + 1>), dim3(nb),                               \
-                           dim3((((NN + 1) * (NN + 1) * (NN + 1) + 63) / 64) * 64), 0, s, d, q, \
+        hipLaunchKernelGGL((sem::k_features<NN + 1>), dim3(unsigned(d.n_col) * sem::pass_chunks<NN + 1>(d.n_z)), \
+                           dim3(sem::pass_threads<NN + 1>()), 0, s, d, q,                     \
                            q_prev, plain, criterion, T, lvl_max, S, feat, M->feat_aux, dem);  \
         break;
         CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
@@ -357,7 +422,7 @@ static int sem_max_wind_impl(const sem_mesh* M, const double* q, double x0, doub
     if (!q || !vmax) return fail(SEM_ERR_ARG, "null array");
     if (!(x0 <= x1 && y0 <= y1)) return fail(SEM_ERR_ARG, "empty box");
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(sem::k_max_wind, dim3(sem::WIND_BLOCKS), dim3(256), 0, s, M->d, q, M->d_hxy,
+    hipLaunchKernelGGL(sem::k_max_wind, dim3(sem::WIND_BLOCKS), dim3(sem::WIND_THREADS), 0, s, M->d, q, M->d_hxy,
                        x0, x1, y0, y1, M->wind_part);
     HIPCHK(hipGetLastError());
     hipLaunchKernelGGL(sem::k_max_wind_final, dim3(1), dim3(256), 0, s, M->wind_part,
