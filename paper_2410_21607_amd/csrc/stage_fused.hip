@@ -42,6 +42,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <type_traits>
 
@@ -1326,13 +1327,13 @@ uint64_t spread_bits(uint64_t x) {
 struct Arena {
     static constexpr size_t CHUNK = size_t(2) << 20;
     FusedPlan& P;
-    std::vector<char> host;
+    std::unique_ptr<char[]> host;
     char* dev = nullptr;
-    size_t cap = 0;
+    size_t used = 0, cap = 0;
     explicit Arena(FusedPlan& plan) : P(plan) {}
     int flush() {
-        const bool ok = host.empty() || hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice) == hipSuccess;
-        host.clear();
+        const bool ok = used == 0 || hipMemcpy(dev, host.get(), used, hipMemcpyHostToDevice) == hipSuccess;
+        used = cap = 0;
         return ok ? SEM_OK : SEM_ERR_HIP;
     }
     int alloc(size_t bytes, void** dst) {
@@ -1341,20 +1342,22 @@ struct Arena {
         P.bytes += int64_t(bytes);
         return SEM_OK;
     }
-    // device address of a table (null if empty); its contents are there after flush()
+    // device address of a table; its contents are there after flush()
     int put(const void* src, size_t bytes, void** dst) {
-        const size_t at = (host.size() + 255) / 256 * 256;
-        if (!dev || at + bytes > cap) {
+        size_t at = (used + 255) / 256 * 256;
+        if (at + bytes > cap) {
             if (const int rc = flush(); rc != SEM_OK) return rc;
+            const size_t size = std::max(bytes, CHUNK);
+            host.reset(new char[size]);
             void* d = nullptr;
-            cap = std::max(bytes, CHUNK);
-            if (const int rc = alloc(cap, &d); rc != SEM_OK) return rc;
+            if (const int rc = alloc(size, &d); rc != SEM_OK) return rc;
             dev = static_cast<char*>(d);
+            cap = size;
+            at = 0;
         }
-        const size_t o = host.empty() ? 0 : at;
-        host.resize(o + bytes);
-        std::memcpy(host.data() + o, src, bytes);
-        *dst = dev + o;
+        std::memcpy(host.get() + at, src, bytes);
+        used = at + bytes;
+        *dst = dev + at;
         return SEM_OK;
     }
 };
@@ -1383,9 +1386,9 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
                           auto&& set_first) {
         auto mark = [&](const std::vector<int32_t>& ptr, const std::vector<int32_t>& slot, int64_t n) {
             for (int64_t x = 0; x < n; ++x) {
-                int32_t best = -1;
-                for (int32_t q = ptr[x]; q < ptr[x + 1]; ++q)
-                    if (best < 0 || color[unit_of_col[slot[q] / np2]] < color[unit_of_col[best / np2]])
+                int32_t best = ptr[x + 1] > ptr[x] ? slot[ptr[x]] : -1;
+                for (int32_t q = ptr[x] + 1; q < ptr[x + 1]; ++q)
+                    if (color[unit_of_col[slot[q] / np2]] < color[unit_of_col[best / np2]])
                         best = slot[q];
                 if (best >= 0) set_first(best);
             }
@@ -1404,10 +1407,11 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
     };
     // Position map, interpolation rows and contribution buffer of a column
     // launch in which the columns `side_cols` (side_of_col: their index, else
-    // -1) only write their own slots, and the tail that finishes the nodes for
-    // which `in_tail` holds.
+    // -1) only write their own slots, and the tail that finishes the nodes of
+    // those columns and the parents of hanging points, except the ones that
+    // others finish (`done`, by node).
     auto side_tables = [&](const std::vector<int32_t>& side_cols, const std::vector<int32_t>& side_of_col,
-                           const std::vector<char>& done, auto&& in_tail, FusedTables& t, TailTables& T) -> int {
+                           const std::vector<char>& done, FusedTables& t, TailTables& T) -> int {
         int rc;
         // positions of side columns become pseudo hanging points n_hh + k (N+1)^2 + pos
         const int64_t n_pseudo = int64_t(side_cols.size()) * np2;
@@ -1450,14 +1454,17 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
             std::vector<int32_t> th, tsptr(1, 0), tsslot, thptr(1, 0), thh;
             std::vector<double> thw;
             std::vector<uint8_t> tfirst;
+            std::vector<char> at_side(static_cast<size_t>(H.n_h), 0);
+            for (int32_t sc : side_cols)
+                for (int pos = 0; pos < np2; ++pos)
+                    if (const int32_t g = H.gmap[size_t(sc) * np2 + pos]; g >= 0) at_side[g] = 1;
             for (int64_t h = 0; h < H.n_h; ++h) {
-                if (!done.empty() && done[h]) continue;
+                if ((!at_side[h] && hT_row[h] < 0) || (!done.empty() && done[h])) continue;
                 bool any_side = false, any_direct = false;
                 for (int32_t q = H.asm_ptr[h]; q < H.asm_ptr[h + 1]; ++q) {
                     if (is_side(H.asm_slot[q])) any_side = true;
                     else any_direct = true;
                 }
-                if (!in_tail(any_side, hT_row[h] >= 0)) continue;
                 th.push_back(int32_t(h));
                 tfirst.push_back(any_direct ? 0 : 1);
                 for (int32_t q = H.asm_ptr[h]; q < H.asm_ptr[h + 1]; ++q)
@@ -1585,9 +1592,7 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
         });
         for (int32_t sc : side_cols)
             for (int pos = 0; pos < np2; ++pos) first[size_t(sc) * np2 + pos] = 1;
-        if ((rc = side_tables(side_cols, side_of_col, {},
-                              [](bool any_side, bool hanging_parent) { return any_side || hanging_parent; },
-                              P.t, P.tail)) != SEM_OK)
+        if ((rc = side_tables(side_cols, side_of_col, {}, P.t, P.tail)) != SEM_OK)
             return rc;
         P.has_tail = !side_cols.empty();
         if ((rc = up(order.data(), order.size() * 4, &d)) != SEM_OK) return rc;
@@ -1607,10 +1612,15 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
         // a column are regular (a coarse face has none), so that only the
         // positions on its sides are looked at.
         const int N = H.N, np1 = H.np1, HS = own_positions(N);
-        // per node the column that has it at (i, j), by whether i and j are N
-        struct At { int32_t col[4]; int32_t n, lev; };
-        constexpr int32_t NONE = -1, MIXED = -2;
-        std::vector<At> at(static_cast<size_t>(H.n_h), At{{NONE, NONE, NONE, NONE}, 0, NONE});
+        // per node the columns that have it at (N, j) and (i, N), their number
+        // and level, and which of (i, j), (N, j), (i, N), (N, N) it is in them
+        constexpr int8_t NONE = -1, MIXED = -2;
+        struct At {
+            int32_t col[2] = {-1, -1};
+            int8_t n = 0, lev = NONE;
+            uint8_t seen = 0;
+        };
+        std::vector<At> at(static_cast<size_t>(H.n_h));
         std::vector<char> side(static_cast<size_t>(H.n_col), 0), regular(static_cast<size_t>(H.n_h), 1);
         std::vector<uint64_t> mask(static_cast<size_t>(H.n_col), 0);
         std::vector<int32_t> sides;
@@ -1630,9 +1640,11 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
                 }
                 At& x = at[h];
                 const int k = (pos % np1 == N) + 2 * (pos / np1 == N);
-                x.lev = x.col[k] == NONE && (x.lev == NONE || x.lev == H.col_level[cc]) ? H.col_level[cc] : MIXED;
-                x.col[k] = cc;
-                ++x.n;
+                const int8_t lev = int8_t(H.col_level[cc]);
+                x.lev = !(x.seen >> k & 1) && (x.lev == NONE || x.lev == lev) ? lev : MIXED;
+                x.seen |= uint8_t(1 << k);
+                if (k == 1 || k == 2) x.col[k - 1] = cc;
+                x.n = int8_t(std::min(x.n + 1, 5));
             }
         for (int32_t cc = 0; cc < H.n_col; ++cc) {
             mask[cc] = inside;
@@ -1684,7 +1696,7 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
             // sides; for a node not computed here: any rows
             auto across = [&](int x, int k) {
                 const int32_t h = H.gmap[size_t(cc) * np2 + x];
-                return h >= 0 && regular[h] ? at[h].col[k] : cc;
+                return h >= 0 && regular[h] ? at[h].col[k - 1] : cc;
             };
             for (int j = 0; j < N; ++j)
                 for (int i = 0; i < N; ++i) pos(cc, i, j);
@@ -1710,7 +1722,7 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
         P.ot.n = int(own.size());
         P.n_side = int(side_cols.size());
         if (P.n_side > 0) {
-            if ((rc = side_tables(side_cols, side_of_col, regular, [](bool, bool) { return true; }, P.to, P.own_tail)) != SEM_OK)
+            if ((rc = side_tables(side_cols, side_of_col, regular, P.to, P.own_tail)) != SEM_OK)
                 return rc;
             std::vector<uint8_t> first(H.gmap.size(), 1);   // every slot has one writer
             if ((rc = upv(first, &P.to.first)) != SEM_OK) return rc;
