@@ -22,9 +22,9 @@
 //                   over interleaved samples combined in a fixed order
 //                   (deterministic);
 //   k_adam        : element-wise Adam update.
-// Measured on an MI355X at 1024 samples: k_mlp_samples 6.4 us (63 before),
+// Measured on an MI355X at 1024 samples: k_mlp_samples 7 us (63 before),
 // k_mlp_grad 11 (38, a thread per parameter and batch segment); k_mlp_forward
-// on 49,760 rows 12.3 us (58).  A training step is then paced by its three
+// on 49,760 rows 16 us (58).  A training step is then paced by its three
 // launches.
 #include <cmath>
 #include <cstdint>
@@ -65,71 +65,106 @@ __device__ __forceinline__ void st4(float* __restrict__ p, f4 v) {
 }
 
 // lane = 16 g + c of wave w.  A operand of a step: row c, k = g; B: k = g,
-// column c; accumulator: rows 4 g + 0..3, column c.  The k of the steps are
-// taken as 16 t + 4 g + s (any order will do), so that a lane's four steps of
-// one t are four consecutive floats.
+// column c; accumulator: rows 4 g + 0..3, column c.  Step q has the products
+// k = 4 q + g, and the instruction adds its four in that order, one rounding
+// each: every sum is the chain over k = 0, 1, ... that a scalar loop forms, to
+// the bit.  (Adam's first steps turn the rounding of a small gradient into a
+// step of the learning rate, so that another order shows in the parameters.)
 struct Lane { int w, g, c; };
 __device__ __forceinline__ Lane lane_of(int t) { return {t >> 6, (t >> 4) & 3, t & 15}; }
 
+// The 4 x 4 transpose of the values v[s] of the lanes g = 0..3 of a column:
+// lane g's v[s] becomes lane s's v[g] (halves, then quarters of the wave
+// exchanged).  Turns four consecutive values 16 t + 4 g + s into those of four
+// steps, 16 t + 4 s + g, and back.
+__device__ __forceinline__ f4 turn(f4 v) {
+    using u2 = __attribute__((ext_vector_type(2))) unsigned;
+    unsigned x[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = __float_as_uint(v[s]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const u2 y = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(x[s], x[s + 2], false, false));
+        x[s] = y.x;
+        x[s + 2] = y.y;
+    }
+#pragma unroll
+    for (int s = 0; s < 4; s += 2) {
+        const u2 y = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(x[s], x[s + 1], false, false));
+        x[s] = y.x;
+        x[s + 1] = y.y;
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = __uint_as_float(x[s]);
+    return v;
+}
+// Hidden values of a sample in LDS: value 16 t + 4 s + g at 16 t + 4 g + s, so
+// that a lane's values of four steps are consecutive.
+__device__ __forceinline__ void put_hidden(float* row, Lane l, f4 v) {
+    *reinterpret_cast<f4*>(row + 16 * l.w + 4 * l.g) = turn(v);
+}
+// sum over the 64 hidden values: a += A[k] B[k]
+__device__ __forceinline__ f4 chain(const float* A, const float* row, Lane l, f4 a) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const f4 h = *reinterpret_cast<const f4*>(row + 16 * t + 4 * l.g);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a = __builtin_amdgcn_mfma_f32_16x16x4f32(A[4 * t + s], h[s], a, 0, 0, 0);
+    }
+    return a;
+}
 // this lane's share of the parameters
 struct Weights {
-    f4 w1, b1, w2[4], b2, w3[NO];
-    float b3[NO];
+    f4 w1, b1, b2, b3, w3[NO];     // w3: of the lane's hidden units
+    float w2[16], z3[16];          // z3: row c of the output layer (c < NO)
     template <bool AL>
     __device__ __forceinline__ void load(const float* __restrict__ p, Lane l) {
         const int row = 16 * l.w + l.c, r4 = 16 * l.w + 4 * l.g;
-        w1 = ld4<AL>(p + OW1 + row * NI + 4 * l.g);
+        w1 = turn(ld4<AL>(p + OW1 + row * NI + 4 * l.g));
         b1 = ld4<AL>(p + OB1 + r4);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) w2[t] = ld4<AL>(p + OW2 + row * NH + 16 * t + 4 * l.g);
         b2 = ld4<AL>(p + OB2 + r4);
+        const int o = min(l.c, NO - 1);
 #pragma unroll
-        for (int o = 0; o < NO; ++o) {
-            w3[o] = ld4<AL>(p + OW3 + o * NH + r4);
-            b3[o] = p[OB3 + o];
+        for (int t = 0; t < 4; ++t) {
+            const f4 a = turn(ld4<AL>(p + OW2 + row * NH + 16 * t + 4 * l.g));
+            const f4 b = turn(ld4<AL>(p + OW3 + o * NH + 16 * t + 4 * l.g));
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                w2[4 * t + s] = a[s];
+                z3[4 * t + s] = b[s];
+            }
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b3[r] = p[OB3 + min(r, NO - 1)];
+#pragma unroll
+        for (int r = 0; r < NO; ++r) w3[r] = ld4<AL>(p + OW3 + r * NH + r4);
     }
 };
 
 struct Tile {
     float h1[TS][HS];              // first hidden layer, then reused for d2
-    float z[4][NO][TS];            // the waves' parts of the logits
+    float h2[TS][HS];
 };
 
-// Hidden values of units 16w + 4g + 0..3 of sample c, and its logits (every
-// lane of column c holds them).  Two barriers; the tile may be written again
-// after the second.
-__device__ __forceinline__ void forward_tile(const Weights& W, f4 x, Lane l, Tile& T, f4& h1, f4& h2,
-                                             float* z3) {
+// Hidden values of units 16w + 4g + 0..3 of sample c.  Two barriers; after the
+// second T.h2 holds the second layer and T.h1 may be written again.
+__device__ __forceinline__ void forward_tile(const Weights& W, f4 x, Lane l, Tile& T, f4& h1, f4& h2) {
     f4 a = W.b1;
 #pragma unroll
     for (int s = 0; s < 4; ++s) a = __builtin_amdgcn_mfma_f32_16x16x4f32(W.w1[s], x[s], a, 0, 0, 0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) h1[r] = tanhf(a[r]);
-    st4<true>(&T.h1[l.c][16 * l.w + 4 * l.g], h1);
+    put_hidden(T.h1[l.c], l, h1);
     __syncthreads();
-    a = W.b2;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const f4 h = ld4<true>(&T.h1[l.c][16 * t + 4 * l.g]);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) a = __builtin_amdgcn_mfma_f32_16x16x4f32(W.w2[t][s], h[s], a, 0, 0, 0);
-    }
+    a = chain(W.w2, T.h1[l.c], l, W.b2);
 #pragma unroll
     for (int r = 0; r < 4; ++r) h2[r] = tanhf(a[r]);
-#pragma unroll
-    for (int o = 0; o < NO; ++o) {
-        float s = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s = fmaf(W.w3[o][r], h2[r], s);
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        if (l.g == 0) T.z[l.w][o][l.c] = s;
-    }
+    put_hidden(T.h2[l.c], l, h2);
     __syncthreads();
-#pragma unroll
-    for (int o = 0; o < NO; ++o)
-        z3[o] = W.b3[o] + ((T.z[0][o][l.c] + T.z[1][o][l.c]) + (T.z[2][o][l.c] + T.z[3][o][l.c]));
+}
+// the logits of sample c: rows 0..2 of the product, in the lanes of g = 0
+__device__ __forceinline__ f4 logits_tile(const Weights& W, Lane l, const Tile& T) {
+    return chain(W.z3, T.h2[l.c], l, W.b3);
 }
 
 }  // namespace
@@ -143,12 +178,19 @@ k_mlp_forward(const float* __restrict__ p, const float* __restrict__ x, int64_t 
     Weights W;
     W.load<AL>(p, l);
     const int64_t nt = (n + TS - 1) / TS;
+    int turn_of = 0;
     for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
         const int64_t b = t * TS + l.c;
         f4 h1, h2;
-        float z3[NO];
-        forward_tile(W, ld4<AL>(x + min(b, n - 1) * NI + 4 * l.g), l, T, h1, h2, z3);
-        if (l.w == 0 && l.g < NO && b < n) logits[b * NO + l.g] = l.g == 0 ? z3[0] : l.g == 1 ? z3[1] : z3[2];
+        forward_tile(W, turn(ld4<AL>(x + min(b, n - 1) * NI + 4 * l.g)), l, T, h1, h2);
+        // (a wave in turn; the next tile's second barrier frees T.h2)
+        if (l.w == turn_of) {
+            const f4 z = logits_tile(W, l, T);
+            if (l.g == 0 && b < n)
+#pragma unroll
+                for (int o = 0; o < NO; ++o) logits[b * NO + o] = z[o];
+        }
+        turn_of = (turn_of + 1) & 3;
     }
 }
 
@@ -165,15 +207,19 @@ k_mlp_samples(const float* __restrict__ p, const float* __restrict__ x,
     // the second layer transposed: row 16w + c of W2^T
     float wt[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) wt[k] = p[OW2 + (16 * (k / 4) + 4 * l.g + k % 4) * NH + 16 * l.w + l.c];
+    for (int q = 0; q < 16; ++q) wt[q] = p[OW2 + (4 * q + l.g) * NH + 16 * l.w + l.c];
     const int64_t nt = (n + TS - 1) / TS;
     for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
         const int64_t b = t * TS + l.c, bc = min(b, n - 1);
         const int64_t s = idx ? min(max(int64_t(idx[bc]), int64_t(0)), n_rows - 1) : bc;
         const int lab = min(max(int(cls[s]), 0), NO - 1);
         f4 h1, h2;
+        forward_tile(W, turn(ld4<AL>(x + s * NI + 4 * l.g)), l, T, h1, h2);
+        // (each wave forms the logits, whose lanes all need them)
+        const f4 z = logits_tile(W, l, T);
         float z3[NO];
-        forward_tile(W, ld4<AL>(x + s * NI + 4 * l.g), l, T, h1, h2, z3);
+#pragma unroll
+        for (int o = 0; o < NO; ++o) z3[o] = __shfl(z[o], l.c);
         // softmax and cross-entropy
         const float zm = fmaxf(z3[0], fmaxf(z3[1], z3[2]));
         float ex[NO], se = 0.0f, zl = z3[0];
@@ -196,16 +242,10 @@ k_mlp_samples(const float* __restrict__ p, const float* __restrict__ x,
             d2[r] = s2 * (1.0f - h2[r] * h2[r]);
         }
         const int r4 = 16 * l.w + 4 * l.g;
-        st4<true>(&T.h1[l.c][r4], d2);
+        put_hidden(T.h1[l.c], l, d2);
         __syncthreads();
         // layer 1 error: (W2^T d2) * (1 - h1^2)
-        f4 a = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const f4 d = ld4<true>(&T.h1[l.c][16 * k + 4 * l.g]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) a = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[4 * k + q], d[q], a, 0, 0, 0);
-        }
+        const f4 a = chain(wt, T.h1[l.c], l, f4{0.0f, 0.0f, 0.0f, 0.0f});
         __syncthreads();               // the tile is written again by the next samples
         if (b >= n) continue;
         f4 d1;
