@@ -1130,7 +1130,8 @@ k_stage_blocks(DevMesh m, BlockTables bt, int b0, int nblk, int seg_par, int n_i
 // receives side-slot contributions or hanging-point contributions (Z^T) sums
 // them in a fixed order and is finished here: written whole when no column
 // launch wrote it first, else added to.
-__global__ void k_stage_tail(DevMesh m, TailTables tl, double a, double b, double c,
+__global__ void __launch_bounds__(256)
+k_stage_tail(DevMesh m, TailTables tl, double a, double b, double c,
                              const double* __restrict__ qn, const double* __restrict__ qs,
                              double* __restrict__ qo) {
     const int nzn = m.nzn;
@@ -1163,20 +1164,40 @@ __global__ void k_stage_tail(DevMesh m, TailTables tl, double a, double b, doubl
         // and then added times its weight
         double s[NF] = {0, 0, 0, 0, 0}, v[NF] = {0, 0, 0, 0, 0};
         double wc = 0.0;
-        for (int e = tl.eptr[li]; e < tl.eptr[li + 1]; ++e) {
-            if (tl.estart[e]) {
+        // (four rows' loads at once: one at a time each waits two round trips)
+        constexpr int U = 4;
+        const int e1 = tl.eptr[li + 1];
+        for (int e0 = tl.eptr[li]; e0 < e1; e0 += U) {
+            int row[U];
+            bool start[U];
+            double w[U], x[U][NF];
 #pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    s[f] += wc * v[f];
-                    v[f] = 0.0;
-                }
-                wc = tl.ew[e];
+            for (int u = 0; u < U; ++u) {
+                const int e = min(e0 + u, e1 - 1);
+                row[u] = tl.erow[e];
+                start[u] = tl.estart[e] != 0;
+                w[u] = tl.ew[e];
             }
-            const int row = tl.erow[e];
-            if (row >= 0) {
-                const int64_t o = int64_t(row) * m.ldz + kz;
 #pragma unroll
-                for (int f = 0; f < NF; ++f) v[f] += tl.cH[f * fsh + o];
+            for (int u = 0; u < U; ++u) {
+                const int64_t o = int64_t(max(row[u], 0)) * m.ldz + kz;
+#pragma unroll
+                for (int f = 0; f < NF; ++f) x[u][f] = tl.cH[f * fsh + o];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (e0 + u >= e1) break;
+                if (start[u]) {
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        s[f] += wc * v[f];
+                        v[f] = 0.0;
+                    }
+                    wc = w[u];
+                }
+                if (row[u] >= 0)
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) v[f] += x[u][f];
             }
         }
 #pragma unroll
