@@ -1755,8 +1755,15 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
                              [&](int32_t x, int32_t y) { return n_hang[x] > n_hang[y]; });
             if ((rc = upv(side_cols, &P.to.col_order)) != SEM_OK) return rc;
             P.to.n_color = 1;
-            P.to.layers_per_chunk = lpc;
-            P.to.thread_order = P.t.thread_order;
+            // a few hundred columns, paced by the latency of their chunks: the
+            // deepest chunk, natural order.  us per stage with 2, 4 and 8
+            // layers per chunk: two levels over 64 x 64 x 8 elements at N = 4
+            // 170, 164, 161; three over 20 x 20 x 16 102, 91, 84; with 1 and 2
+            // two over 20 x 20 x 6 at N = 6 143, 134
+            P.to.layers_per_chunk = 1;
+            while (P.to.layers_per_chunk < H.n_z && fused_lpc_supported(N, 2 * P.to.layers_per_chunk))
+                P.to.layers_per_chunk *= 2;
+            P.to.thread_order = 1;
         }
         P.own = true;
     }
