@@ -59,7 +59,11 @@ constexpr int NF = SEM_NFIELDS;
 
 template <int NP, int LPC, bool SE = false>
 constexpr int wg_threads() {
-    return ((NP * NP * (SE ? LPC * NP : LPC * (NP - 1) + 1) + 63) / 64) * 64;
+    // a thread per node, and per entry of a chunk's slice of the vertical
+    // tables (more than the nodes at N = 1 with eight layers)
+    constexpr int nodes = NP * NP * (SE ? LPC * NP : LPC * (NP - 1) + 1);
+    constexpr int slice = 6 * (LPC * (NP - 1) + 1) + 2 * LPC;
+    return ((nodes > slice ? nodes : slice) + 63) / 64 * 64;
 }
 
 // Split-element thread order: a thread per (element, local node) of each
