@@ -1648,42 +1648,48 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
         std::vector<At> at(static_cast<size_t>(H.n_h));
         std::vector<char> side(static_cast<size_t>(H.n_col), 0), regular(static_cast<size_t>(H.n_h), 1);
         std::vector<uint64_t> mask(static_cast<size_t>(H.n_col), 0);
-        std::vector<int32_t> sides;
+        // positions on the column's sides: which of the four places above, the
+        // owner's bit of the node (its i or j is 0 where it is N here), the
+        // columns that share a regular one
+        struct Side { int32_t pos; int8_t k, bit, n; };
+        std::vector<Side> sides;
         uint64_t inside = 0;
         for (int pos = 0; pos < np2; ++pos) {
-            const int i = pos % np1, j = pos / np1;
-            if (i == 0 || j == 0 || i == N || j == N) sides.push_back(pos);
+            const int i = pos % np1, j = pos / np1, oi = i % N, oj = j % N;
+            if (oi == 0 || oj == 0)
+                sides.push_back({pos, int8_t((i == N) + 2 * (j == N)), int8_t(oi + N * oj),
+                                 int8_t((oi == 0 ? 2 : 1) * (oj == 0 ? 2 : 1))});
             else inside |= uint64_t(1) << (i + N * j);
         }
         for (int32_t h : H.hT_list) at[h].lev = MIXED;
-        for (int32_t cc = 0; cc < H.n_col; ++cc)
-            for (int32_t pos : sides) {
-                const int32_t h = H.gmap[size_t(cc) * np2 + pos];
+        for (int32_t cc = 0; cc < H.n_col; ++cc) {
+            const int32_t* g = &H.gmap[size_t(cc) * np2];
+            const int8_t lev = int8_t(H.col_level[cc]);
+            for (const Side& p : sides) {
+                const int32_t h = g[p.pos];
                 if (h < 0) {
                     side[cc] = 1;
                     continue;
                 }
                 At& x = at[h];
-                const int k = (pos % np1 == N) + 2 * (pos / np1 == N);
-                const int8_t lev = int8_t(H.col_level[cc]);
-                x.lev = !(x.seen >> k & 1) && (x.lev == NONE || x.lev == lev) ? lev : MIXED;
-                x.seen |= uint8_t(1 << k);
-                if (k == 1 || k == 2) x.col[k - 1] = cc;
+                x.lev = !(x.seen >> p.k & 1) && (x.lev == NONE || x.lev == lev) ? lev : MIXED;
+                x.seen |= uint8_t(1 << p.k);
+                if (p.k == 1 || p.k == 2) x.col[p.k - 1] = cc;
                 x.n = int8_t(std::min(x.n + 1, 5));
             }
+        }
         for (int32_t cc = 0; cc < H.n_col; ++cc) {
+            const int32_t* g = &H.gmap[size_t(cc) * np2];
             mask[cc] = inside;
-            for (int32_t pos : sides) {
-                const int32_t h = H.gmap[size_t(cc) * np2 + pos];
+            for (const Side& p : sides) {
+                const int32_t h = g[p.pos];
                 if (h < 0) continue;
                 const At& x = at[h];
-                // the owner's position of the node: 0 where it is N here
-                const int i = pos % np1 % N, j = pos / np1 % N;
-                if (x.lev == MIXED || x.n != (i == 0 ? 2 : 1) * (j == 0 ? 2 : 1)) {
+                if (x.lev == MIXED || x.n != p.n) {
                     side[cc] = 1;
                     regular[h] = 0;
-                } else if (pos % np1 < N && pos / np1 < N) {
-                    mask[cc] |= uint64_t(1) << (i + N * j);
+                } else if (p.k == 0) {
+                    mask[cc] |= uint64_t(1) << p.bit;
                 }
             }
         }
