@@ -44,7 +44,7 @@ __device__ __forceinline__ double root(double x) { return x >= 0.0 ? sqrt(x) : x
 // reference).  dem = number of thresholds the criterion's element maximum
 // exceeds (the level the criterion asks for).
 //
-// 6,220 columns of 8 layers at N = 4 (three levels): 142 us, 0.28 GB read; 320
+// 6,220 columns of 8 layers at N = 4 (three levels): 142 us, 0.56 GB read; 320
 // with a workgroup per element and a thread per node, whose 14 results took a
 // wave reduction each.  What is left is latency at ten waves per CU (LDS), half
 // of it the wait for the nodes; VALU issue is 40 %.

@@ -59,11 +59,7 @@ constexpr int NF = SEM_NFIELDS;
 
 template <int NP, int LPC, bool SE = false>
 constexpr int wg_threads() {
-    // a thread per node, and per entry of a chunk's slice of the vertical
-    // tables (more than the nodes at N = 1 with eight layers)
-    constexpr int nodes = NP * NP * (SE ? LPC * NP : LPC * (NP - 1) + 1);
-    constexpr int slice = 6 * (LPC * (NP - 1) + 1) + 2 * LPC;
-    return ((nodes > slice ? nodes : slice) + 63) / 64 * 64;
+    return ((NP * NP * (SE ? LPC * NP : LPC * (NP - 1) + 1) + 63) / 64) * 64;
 }
 
 // Split-element thread order: a thread per (element, local node) of each
@@ -190,7 +186,16 @@ k_stage_columns(DevMesh m, FusedTables ft, int col0, int ncol, double a, double 
         if constexpr (TER) return (sl_src && k < sl_lim) ? sl_src[k] : 0.0;
         else return k < sl_lim ? sl_src[k] : 0.0;
     };
+    // entries past the workgroup's threads (N = 1 with eight layers: the last
+    // six of 70): the first threads take those too
+    constexpr int MORE = SL > WGT ? SL - WGT : 0;
+    static_assert(MORE == 0 || (WGT >= 6 * NK && MORE <= WGT), "the entries past the threads are the layers'");
+    auto slice_more = [&](int ch2) {
+        const int e = WGT + tid - 6 * NK, k = (e < LPC ? e : e - LPC) + ch2 * LPC;
+        return k < m.n_z ? (e < LPC ? m.dz : m.sz)[k] : 0.0;
+    };
     if (tid < SL) slice[0][tid] = slice_value(0);
+    if (MORE > 0 && tid < MORE) slice[0][WGT + tid] = slice_more(0);
 
     // Workgroups start in block order (and go to the 8 XCDs round-robin);
     // the plan lists each colour's columns by decreasing work, so that the
@@ -429,6 +434,8 @@ k_stage_columns(DevMesh m, FusedTables ft, int col0, int ncol, double a, double 
         const double* sb = slice[ch & 1];
         double sl_next = 0.0;
         if (tid < SL && ch + 1 < n_chunk) sl_next = slice_value(ch + 1);
+        double sl_more = 0.0;
+        if (MORE > 0 && tid < MORE && ch + 1 < n_chunk) sl_more = slice_more(ch + 1);
         // prefetch the next chunk's q_s (PRE: box elements, and terrain in
         // the split-element order; the other terrain instances need those
         // registers for their metric terms)
@@ -730,6 +737,7 @@ k_stage_columns(DevMesh m, FusedTables ft, int col0, int ncol, double a, double 
             }
         }
         if (tid < SL && ch + 1 < n_chunk) slice[(ch + 1) & 1][tid] = sl_next;
+        if (MORE > 0 && tid < MORE && ch + 1 < n_chunk) slice[(ch + 1) & 1][WGT + tid] = sl_more;
         __syncthreads();
     }
 }

@@ -12,8 +12,8 @@
 // columns' derivatives (equal masses), and the neighbour's comes from one line
 // of N nodes per face node, the halo lines.  They are reduced to their sums of
 // D(N, m) f_m while they are loaded, so that the tiles hold the column's own
-// nodes only.  q_out is written once and q_s read 1.06 times (the lines are in
-// the XCD's L2: neighbours run on it at the same time).
+// nodes only.  q_out is written once; q_s is read from beyond the L2 about 1.5
+// times (most halo lines are in it: an XCD's columns are neighbours).
 //
 // A workgroup marches up its column in chunks of LPC elements, a thread per
 // owned node:
@@ -25,11 +25,11 @@
 //     finishes the top lid; barrier.
 //
 // What bounds it (N = 4, 64 x 64 x 16 elements): 178 us per stage against 231
-// for the four colour launches, 0.40 GB of HBM traffic per stage against
-// 0.99.  The memory is no longer the limit (78 us at the copy rate): without
-// any loads and stores the kernel takes 131 us, VALU issue is 40 % and LDS 31 %
-// of the time, 10 of 12 waves per CU resident; the rest is latency of the
-// chunk's chain load - tiles - barrier - derivatives.
+// for the four colour launches, 0.69 GB of traffic per stage against 0.99
+// (0.52 read, 0.18 written; 136 us at the copy rate).  Without any loads and
+// stores the kernel takes 131 us, VALU issue is 40 % and LDS 31 % of the time,
+// 10 of 12 waves per CU resident: memory and on-chip work overlap but for the
+// latency of the chunk's chain load - tiles - barrier - derivatives.
 #include "stage_fused.h"
 
 #include <hip/hip_runtime.h>
