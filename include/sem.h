@@ -329,7 +329,8 @@ int sem_stage_get_tune(const sem_mesh *mesh, int *layers_per_chunk);
  *     the column in `param` vertical segments (0 = enough segments for about
  *     1024 workgroups per launch); columns in no block run as in the column
  *     layout.  Orders 3 to 5 on meshes with blocks (box elements: with
- *     terrain set, sem_stage runs the column layout).
+ *     terrain set, sem_stage runs the column layout, as it does where a block
+ *     or column is its own neighbour across a periodic side).
  * The faces inside a block are summed in the workgroup; blocks are coloured
  * like columns, so the results are deterministic in either layout (they
  * differ between layouts by the order of the sums, within 1e-14).  Meshes

@@ -1397,7 +1397,7 @@ static int sem_stage_autotune_impl(sem_mesh* M, const double* qn, const double* 
                     cand.push_back({SEM_LAYOUT_COLUMNS_SPLIT, lpc});
             }
         }
-    if (sem::fused_blocks_supported(M->host) && !M->d.zs) {
+    if (sem::fused_blocks_supported(M->host) && !M->d.zs && !sem::fused_blocks_wrap(M->host)) {
         int last_ls = -1;
         for (int S = 1; S <= M->host.n_z; S *= 2) {
             const int ls = (M->host.n_z + S - 1) / S;

@@ -33,7 +33,8 @@ struct FusedTables {
                                 // 2 = split element
     // Position map and interpolation rows the kernel reads (the mesh's own,
     // extended when the plan has side columns).  Side columns (the columns
-    // of the small colour classes of an uneven mesh) run in the launches of
+    // of the small colour classes of an uneven mesh, and those that are their
+    // own neighbour across a periodic side) run in the launches of
     // the other colours, spread to even them out; every position of theirs
     // maps to a pseudo hanging
     // point past the mesh's n_hh, whose row is the unit row of its node (or a
@@ -118,6 +119,7 @@ struct FusedPlan {
     FusedTables ts{};                     // block layout: the columns in no block
     std::vector<int32_t> blk_ptr_host, single_ptr_host;   // per colour
     int n_unit_color = 0;
+    bool blk_wrap = false;                // fused_blocks_wrap: the stage runs the column layout
     std::vector<void*> allocs;
     int64_t bytes = 0;
 };
@@ -132,6 +134,9 @@ bool fused_lpc_supported(int N, int layers_per_chunk);
 // chunk, every pair of threads of a plane node in one wave)
 bool fused_split_supported(int N, int layers_per_chunk);
 bool fused_blocks_supported(const HostMesh& H);
+// whether a block, or a column in no block, touches itself across a periodic
+// side: two of its positions are then one node
+bool fused_blocks_wrap(const HostMesh& H);
 
 // Whether sem_stage evaluates the optional dissipation inside the column
 // kernel (FP64, box elements, column layout) instead of a pre-pass.

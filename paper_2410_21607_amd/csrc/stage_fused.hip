@@ -1314,6 +1314,26 @@ bool fused_blocks_supported(const HostMesh& H) {
 
 namespace {
 
+// whether the columns lo and hi of one level, hi further along x (dir = 0) or
+// y, or the same column, close on themselves across the periodic side: the
+// lower side of lo is then the upper side of hi
+bool wraps(const HostMesh& H, int32_t lo, int32_t hi, int dir) {
+    const int np2 = H.np1 * H.np1;
+    return H.gmap[size_t(lo) * np2] == H.gmap[size_t(hi) * np2 + (dir == 0 ? H.N : H.N * H.np1)];
+}
+
+}  // namespace
+
+bool fused_blocks_wrap(const HostMesh& H) {
+    for (size_t b = 0; b < H.blk_cols.size(); b += 4)
+        if (wraps(H, H.blk_cols[b], H.blk_cols[b + 1], 0) || wraps(H, H.blk_cols[b], H.blk_cols[b + 2], 1)) return true;
+    for (int32_t c = 0; c < H.n_col; ++c)
+        if (H.col_block[c] < 0 && (wraps(H, c, c, 0) || wraps(H, c, c, 1))) return true;
+    return false;
+}
+
+namespace {
+
 // greedy colouring in the given order of units that conflict when they
 // contribute to a common unique node or hanging point; returns the colours
 std::vector<int32_t> colour_units(const HostMesh& H, const std::vector<int32_t>& unit_of_col,
@@ -1571,15 +1591,20 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
         // than a quarter of the largest class's columns.  Their launches
         // would be short and latency-bound; instead they run in the launches
         // of the other colours (they only read q_s and write their own
-        // slots) and the tail launch assembles their contributions.
+        // slots) and the tail launch assembles their contributions.  So do
+        // columns that are their own neighbour (a periodic direction one
+        // column wide): two of their threads have the same node, which a
+        // launch that updates nodes in place would write twice at once.
+        std::vector<char> self(static_cast<size_t>(H.n_col), 0);
+        for (int cidx = 0; cidx < H.n_col; ++cidx) self[cidx] = wraps(H, cidx, cidx, 0) || wraps(H, cidx, cidx, 1);
         std::vector<int32_t> csize(size_t(n_color), 0);
-        for (int cidx = 0; cidx < H.n_col; ++cidx) ++csize[color[cidx]];
+        for (int cidx = 0; cidx < H.n_col; ++cidx) csize[color[cidx]] += !self[cidx];
         const int32_t cmax = *std::max_element(csize.begin(), csize.end());
         std::vector<char> small(size_t(n_color), 0);
         for (int k = 4; k < n_color; ++k) small[k] = 4 * csize[k] < cmax;
         std::vector<int32_t> side_of_col(static_cast<size_t>(H.n_col), -1), side_cols;
         for (int cidx = 0; cidx < H.n_col; ++cidx)
-            if (small[color[cidx]]) {
+            if (small[color[cidx]] || self[cidx]) {
                 side_of_col[cidx] = int32_t(side_cols.size());
                 side_cols.push_back(cidx);
             }
@@ -1608,7 +1633,7 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
             if (small[k]) continue;
             const size_t k0 = order.size();
             for (int cidx = 0; cidx < H.n_col; ++cidx)
-                if (color[cidx] == k) order.push_back(cidx);
+                if (color[cidx] == k && !self[cidx]) order.push_back(cidx);
             order.insert(order.end(), side_of_k[k].begin(), side_of_k[k].end());
             std::stable_sort(order.begin() + k0, order.end(),
                              [&](int32_t x, int32_t y) { return n_hang[x] > n_hang[y]; });
@@ -1899,6 +1924,7 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
     P.blk_ptr_host = bptr;
     P.single_ptr_host = sptr;
     P.n_unit_color = n_color;
+    P.blk_wrap = fused_blocks_wrap(H);
     P.layout = SEM_LAYOUT_BLOCKS;
     return SEM_OK;
 }
@@ -1935,8 +1961,14 @@ int launch_blocks(const DevMesh& m, const BlockTables& bt, int b0, int nblk, int
     return (hipGetLastError() == hipSuccess) ? SEM_OK : SEM_ERR_HIP;
 }
 
+// The block layout's own launches: box elements, and no block or column beside
+// itself across a periodic side (fused_blocks_wrap).
+static bool runs_blocks(const DevMesh& m, const FusedPlan& P) {
+    return P.layout == SEM_LAYOUT_BLOCKS && !P.blk_wrap && !m.zs;
+}
+
 bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& P, int prec) {
-    return (m.cs > 0.0 || m.sponge) && !m.zs && prec == SEM_FP64 && P.layout != SEM_LAYOUT_BLOCKS;
+    return (m.cs > 0.0 || m.sponge) && !m.zs && prec == SEM_FP64 && !runs_blocks(m, P);
 }
 
 // The owner kernel takes over where it has an instance (N >= 2).  us per stage,
@@ -1971,7 +2003,7 @@ int fused_stage_launch(const DevMesh& m_in, const FusedPlan& P, double a, double
     const bool diss = fused_dissipation_inline(m_in, P, prec);
     DevMesh m = m_in;
     if (diss) m.rx = nullptr;
-    if (P.layout == SEM_LAYOUT_BLOCKS && !m.zs) {
+    if (runs_blocks(m, P)) {
         // colour by colour: the colour's blocks, even segments then odd
         // ones, then its columns in no block
         const BlockTables& bt = P.bt;
@@ -2028,7 +2060,7 @@ int fused_stage_launch(const DevMesh& m_in, const FusedPlan& P, double a, double
             if (rc != SEM_OK) return rc;
         }
     }
-    const bool tail = P.has_tail && !(P.layout == SEM_LAYOUT_BLOCKS && !m.zs);
+    const bool tail = P.has_tail && !runs_blocks(m, P);
     const int64_t n2 = int64_t(tail ? P.tail.n : m.n_hT) * m.nzn;
     if (n2 > 0) {
         const int64_t g = std::min<int64_t>((n2 + 255) / 256, 65536);
