@@ -91,7 +91,7 @@ def cpu_baseline(plan=(("vortex_8x8x4_n4", 10), (WORKLOAD, 3))):
 def kernel_source_hash():
     """Hash of the fused-stage kernel source (to detect stale counter data)."""
     h = hashlib.sha256()
-    for f in ("stage_fused.hip", "stage_own.hip", "stage_fused.h", "devmesh.h", "nodeval.h"):
+    for f in ("stage_fused.hip", "stage_own.hip", "stage_fused.h", "devmesh.h", "nodeval.h", "rows.h"):
         with open(os.path.join(ROOT, "paper_2410_21607_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

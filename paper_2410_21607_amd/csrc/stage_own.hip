@@ -35,6 +35,7 @@
 #include <hip/hip_runtime.h>
 
 #include "nodeval.h"
+#include "rows.h"
 #include "sem.h"
 
 namespace sem {
@@ -51,13 +52,12 @@ constexpr int own_threads() {
 }
 
 // State arrays are read and written through buffer descriptors: a lane with
-// nothing to load or store takes the offset NOWHERE, which the hardware's range
-// check drops, so that every load and store is issued unconditionally.  Behind
+// nothing to load or store takes the offset NOWHERE (rows.h), which the hardware's
+// range check drops, so that every load and store is issued unconditionally.  Behind
 // a branch the compiler cannot count them and waits for all of them (the next
 // chunk's loads and earlier stores included) at each use: 194 us per stage
 // against 177 on 64 x 64 x 16 elements at N = 4.  32-bit byte offsets: the
 // five fields have to fit in 2 GiB (own_fits).
-constexpr unsigned NOWHERE = 0x80000000u;
 using rsrc_t = __amdgpu_buffer_rsrc_t;
 using u32x2 = __attribute__((ext_vector_type(2))) unsigned;
 __device__ __forceinline__ rsrc_t state_rsrc(const double* p, int64_t n) {
@@ -97,7 +97,7 @@ k_stage_own(DevMesh m, OwnTables ot, double a, double b, double c, const double*
     __shared__ double carry[2][6][P2];
     __shared__ double2 sDxy[P2 * NP];
     __shared__ double sD[NP * NP];
-    __shared__ unsigned s_row[HS];                     // byte offset of the row in a field, or -(hanging point + 1)
+    __shared__ unsigned s_row[HS];                     // row_offset
     // what only the columns with hanging positions and far pressures need
     struct Slow {
         const int32_t *ptr, *src;
@@ -120,10 +120,7 @@ k_stage_own(DevMesh m, OwnTables ot, double a, double b, double c, const double*
     const int xcd = blockIdx.x & 7;
     const int item = xcd * (G >> 3) + min(xcd, G & 7) + (blockIdx.x >> 3);
 
-    for (int t = tc; t < HS; t += WGT) {
-        const int g = ot.map[int64_t(item) * HS + t];
-        s_row[t] = g >= 0 ? unsigned(g) * unsigned(m.ldz) * 8u : unsigned(g);
-    }
+    for (int t = tc; t < HS; t += WGT) s_row[t] = row_offset(ot.map[int64_t(item) * HS + t], m.ldz);
     for (int t = tc; t < 7 * nzn; t += WGT) s_lev[t] = m.lev[t];
     for (int t = tc; t < NP * NP; t += WGT) sD[t] = m.D[t];
     for (int t = tc; t < 2 * 6 * P2; t += WGT) (&carry[0][0][0])[t] = 0.0;
@@ -270,7 +267,7 @@ k_stage_own(DevMesh m, OwnTables ot, double a, double b, double c, const double*
                 if (!place(tc, s, nk, tops, ps, kz)) continue;
                 const unsigned r = s_row[ps];
                 const bool direct = r < NOWHERE;
-                const int hh = direct ? 0 : -int(r) - 1;
+                const int hh = direct ? 0 : row_hanging(r);
                 const int t0 = direct ? 0 : S.ptr[hh], t1 = direct ? 1 : S.ptr[hh + 1];
                 double q[NF] = {0, 0, 0, 0, 0};
 #pragma unroll 1
