@@ -14,6 +14,7 @@
 
 #include "handle.h"
 #include "nodeval.h"
+#include "rows.h"
 
 namespace sem {
 
@@ -310,13 +311,12 @@ k_max_wind(DevMesh m, const double* __restrict__ q, const double* __restrict__ h
         const unsigned x = unsigned(b - first * L) + threadIdx.x, dh = x / L;
         const int64_t h = first + dh;
         if (h >= m.n_h) break;
-        const int k = int(x - dh * L) * 2;
+        const int k = level_pair(int(x - dh * L) * 2, m.nzn);
         const double px = hxy[2 * h], py = hxy[2 * h + 1];
         if (px < x0 || px > x1 || py < y0 || py > y1) continue;
         const vec u = *reinterpret_cast<const vec*>(q + fs + h * m.ldz + k);
         const vec v = *reinterpret_cast<const vec*>(q + 2 * fs + h * m.ldz + k);
-        best = fmax(best, u.x * u.x + v.x * v.x);
-        if (k + 1 < m.nzn) best = fmax(best, u.y * u.y + v.y * v.y);
+        best = fmax(best, fmax(u.x * u.x + v.x * v.x, u.y * u.y + v.y * v.y));
     }
     for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;

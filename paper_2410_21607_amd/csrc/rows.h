@@ -17,4 +17,9 @@ constexpr unsigned row_offset(int g, int ldz) {
 }
 constexpr int row_hanging(unsigned row) { return int((row - NOWHERE) / 8u); }
 
+// First level of the two that a 16-byte access of levels k and k + 1 covers
+// (k < nzn): where k is the last level, the pair below, so that the row's padding
+// is not read (nzn >= 2).
+constexpr int level_pair(int k, int nzn) { return k + 1 < nzn ? k : k - 1; }
+
 }  // namespace sem

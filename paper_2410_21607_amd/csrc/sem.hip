@@ -15,6 +15,7 @@
 #include "adapt.h"
 #include "handle.h"
 #include "nodeval.h"
+#include "rows.h"
 
 namespace sem {
 std::string& last_error() {
@@ -699,13 +700,13 @@ k_transfer(const int32_t* __restrict__ ptr, const int32_t* __restrict__ src,
 #pragma unroll 4
         for (; r < r1; ++r) {
             const double wr = w[r];
-            const double* q = qa + int64_t(src[r]) * ldz + k;
+            const double* q = qa + int64_t(src[r]) * ldz + level_pair(k, nzn);
 #pragma unroll
             for (int f = 0; f < SEM_NFIELDS; ++f) acc[f] += wr * *reinterpret_cast<const vec*>(q + f * fsa);
         }
     };
     auto put = [&](int64_t h, int k, int f, vec v) {
-        if (k + 1 == nzn) v[1] = 0.0;
+        if (k + 1 == nzn) v = vec{v[1], 0.0};             // (level_pair)
         *reinterpret_cast<vec*>(qb + f * fsb + h * ldz + k) = v;
     };
     if (int(blockIdx.x) < n_long) {

@@ -36,3 +36,20 @@ def test_offsets_of_hanging_rows_are_dropped(tmp_path):
     for (int g : {0, 1, 100000})
         if (row_offset(g, ldz) != 8u * 512u * unsigned(g)) { std::printf("node %d\\n", g); return 1; }
     return 0;""")
+
+
+def test_level_pairs_stay_inside_the_row(tmp_path):
+    """The pairs of levels that 16-byte loads take cover every level and none
+    of the padding."""
+    run_host(tmp_path, """
+    for (int nzn = 2; nzn <= 600; ++nzn) {
+        int last = -1;
+        for (int k = 0; k < nzn; k += 2) {
+            const int p = level_pair(k, nzn);
+            if (p < 0 || p + 1 >= nzn) { std::printf("pair %d of %d levels\\n", p, nzn); return 1; }
+            if (p > last + 1) { std::printf("level %d of %d left out\\n", last + 1, nzn); return 1; }
+            last = p + 1;
+        }
+        if (last != nzn - 1) { std::printf("top of %d levels left out\\n", nzn); return 1; }
+    }
+    return 0;""")
