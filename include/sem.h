@@ -271,9 +271,9 @@ int sem_stage_update(const sem_mesh *mesh, double a, double b, double c,
 
 /* Fused stage: d_qout = a*d_qn + b*d_qs + c*R(d_qs), with R the full
  * right-hand side (scatter, element RHS, assembly, gather, finalize, lid rule)
- * evaluated without storing element-local data.  In the column layouts an FP64
- * stage on box elements without dissipation (N >= 2, within 2 GiB of state;
- * N = 7 up to 768 columns) computes every node whose columns have one level
+ * evaluated without storing element-local data.  In the default layout an FP64
+ * stage on box elements without dissipation (N >= 2, within 2 GiB of state and
+ * 512 levels; N = 7 up to 768 columns) computes every node whose columns have one level
  * and surround it in one launch, by the one column that owns it; the columns
  * of the other nodes and the pass that sums theirs are two more launches.
  * Everywhere else work units (columns, or
@@ -295,19 +295,20 @@ int sem_stage(const sem_mesh *mesh, double a, double b, double c,
 
 /* Work decomposition of sem_stage (chosen by the autotuner, or by hand):
  * layers_per_chunk = stacked elements handled by one workgroup of the coloured
- * launches (the owning columns' launch has its own), one thread per
+ * launches, one thread per
  * unique node of the chunk ((N+1)^2 (layers_per_chunk N + 1) threads).
- * 0 = default (the deepest chunk of at most 512 threads).  Supported: 1, 2, 4
+ * 0 = default (the deepest chunk of at most 512 threads, and the owning
+ * columns' launch where it applies; any other value: the coloured launches).  Supported: 1, 2, 4
  * and 8 at N <= 4, 1, 2 and 4 at N = 5, 1 and 2 at N = 6, 7, and 1 at N = 8
  * (workgroups within 1024 threads and a CU's 160 KB of LDS).  Rebuilds
  * the handle's fused tables and synchronises the device.  sem_stage_get_tune
- * reports the current value. */
+ * reports the current value (of the coloured launches). */
 int sem_stage_tune(sem_mesh *mesh, int layers_per_chunk);
 int sem_stage_get_tune(const sem_mesh *mesh, int *layers_per_chunk);
 
 /* Work layout of sem_stage (the LDS tile layout and workgroup packing):
  *   SEM_LAYOUT_COLUMNS: a workgroup per column, chunks of `param` layers
- *     (as sem_stage_tune; 0 = default); in FP64 the threads of the nodes on
+ *     (as sem_stage_tune; 0 = default, with the owning columns' launch); in FP64 the threads of the nodes on
  *     the planes between stacked elements come first (they take two z
  *     derivatives), in float the vertical index runs fastest;
  *   SEM_LAYOUT_COLUMNS_KZ: the same with the vertical index fastest in FP64
@@ -336,16 +337,20 @@ int sem_stage_get_tune(const sem_mesh *mesh, int *layers_per_chunk);
  * differ between layouts by the order of the sums, within 1e-14).  Meshes
  * start in the column layout.  Rebuilds the handle's tables and
  * synchronises the device.  sem_stage_get_layout reports the layout and its
- * parameter (layers per chunk, or the number of segments). */
+ * parameter (layers per chunk, or the number of segments; 0 for the default
+ * layout of a mesh that the owning columns' launch applies to), so that the two
+ * given back to sem_stage_set_layout restore the launches. */
 int sem_stage_set_layout(sem_mesh *mesh, int layout, int param);
 int sem_stage_get_layout(const sem_mesh *mesh, int *layout, int *param);
 
 /* Autotuner: times every supported work layout on this mesh (the column
  * layout at each supported layers_per_chunk, in FP64 in each thread order,
- * the block layout at 1, 2, 4, ... vertical segments; reps fused stages
- * each, HIP events on `stream`, d_qout used as scratch; the default column
- * layout alone of the column ones where sem_stage needs no coloured launches),
- * keeps the fastest with sem_stage_set_layout, and reports
+ * the block layout at 1, 2, 4, ... vertical segments, and the default layout
+ * where the owning columns' launch applies; reps fused stages
+ * each, HIP events on `stream`, d_qout used as scratch),
+ * keeps the fastest as sem_stage_set_layout would (a default layout with the
+ * fastest order and chunk for the stages that need coloured launches; tuned for
+ * such a stage, the others keep the owning columns' launch), and reports
  * it (*best_lpc = the column layout's layers per chunk, see
  * sem_stage_get_layout for the layout; *best_ms = mean stage time in ms;
  * either may be NULL).  Synchronises the stream. */

@@ -50,6 +50,8 @@ class AdaptiveRun:
                  adapt=True, terrain=None):
         """mesh: api.Mesh; q0: padded state tensor on it; reference: tuple of
         (rho0, theta0, dtheta0dz) per vertical node (already set on mesh);
+        layers_per_chunk: 0 (the default layout), or the chunk of the coloured
+        launches (api.sem_stage_tune on every new mesh);
         wind_box: (x0, x1, y0, y1) of the maximum-wind diagnostic (default:
         the whole domain); adapt=False keeps the mesh fixed (diagnostics only);
         terrain: optional callable mesh -> (zs per horizontal node, rho0,

@@ -324,15 +324,16 @@ def sem_stage_set_layout(mesh, layout, param=0):
 
 
 def sem_stage_get_layout(mesh):
-    """(layout, param): layers per chunk of the column layout, or the number
-    of vertical segments of the block layout."""
+    """(layout, param): layers per chunk of the column layout (0: the default
+    layout, where the owner kernel applies), or the number of vertical segments
+    of the block layout."""
     lay, par = ctypes.c_int(), ctypes.c_int()
     native.call("sem_stage_get_layout", mesh.handle, ctypes.byref(lay), ctypes.byref(par))
     return lay.value, par.value
 
 
 def sem_stage_autotune(mesh, qn, qs, qout, precision=SEM_FP64, reps=5, stream=None):
-    """Pick the fastest chunk depth on this mesh; returns (layers_per_chunk, ms)."""
+    """Pick the fastest work layout on this mesh; returns (layers_per_chunk, ms)."""
     n = mesh.n_state
     lpc, ms = ctypes.c_int(), ctypes.c_float()
     native.call("sem_stage_autotune", mesh.handle, _ptr(qn, torch.float64, n, "qn"),

@@ -10,6 +10,7 @@
 #include <memory>
 #include <string>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "adapt.h"
@@ -901,7 +902,7 @@ static int sem_mesh_create_impl(const sem_mesh_desc* desc, sem_mesh** out) {
     HIPCHK(hipMalloc(&M->wind_part, sizeof(double) * 256));
     HIPCHK(hipMalloc(&M->feat_aux, sizeof(double) * 2 * size_t(std::max<int64_t>(1, int64_t(H.n_col) * H.n_z))));
     M->ws_bytes += int64_t(sizeof(double)) * 2 * int64_t(H.n_col) * H.n_z;
-    if ((rc = sem::fused_plan_build(H, SEM_LAYOUT_COLUMNS, 0, M->fused)) != SEM_OK)
+    if ((rc = sem::fused_plan_build(H, SEM_LAYOUT_COLUMNS, 0, M->fused, true)) != SEM_OK)
         return fail(rc, "could not build the fused-stage tables");
     *out = M.release();
     return SEM_OK;
@@ -1337,7 +1338,7 @@ static int sem_stage_set_layout_impl(sem_mesh* M, int layout, int param) {
     if (layout == SEM_LAYOUT_BLOCKS && !sem::fused_blocks_supported(M->host))
         return fail(SEM_ERR_ARG, "no block layout for this mesh (order 3 to 5 with 2 x 2 column blocks)");
     sem::FusedPlan P;
-    int rc = sem::fused_plan_build(M->host, layout, param, P);
+    int rc = sem::fused_plan_build(M->host, layout, param, P, sem::fused_plan_owner(layout, param));
     if (rc != SEM_OK) { sem::fused_plan_free(P); return fail(rc, "could not build the fused-stage tables"); }
     HIPCHK(hipDeviceSynchronize());
     sem::fused_plan_free(M->fused);
@@ -1353,7 +1354,8 @@ int sem_stage_set_layout(sem_mesh* M, int layout, int param) {
 int sem_stage_get_layout(const sem_mesh* M, int* layout, int* param) {
     if (!M || !layout || !param) return fail(SEM_ERR_ARG, "null argument");
     *layout = M->fused.layout;
-    *param = M->fused.layout == SEM_LAYOUT_BLOCKS ? M->fused.bt.n_seg : M->fused.t.layers_per_chunk;
+    *param = M->fused.layout == SEM_LAYOUT_BLOCKS ? M->fused.bt.n_seg
+             : M->fused.own && M->fused.by_default ? 0 : M->fused.t.layers_per_chunk;
     return SEM_OK;
 }
 
@@ -1378,18 +1380,24 @@ static int sem_stage_autotune_impl(sem_mesh* M, const double* qn, const double* 
     if (prec != SEM_FP64 && prec != SEM_FP32) return fail(SEM_ERR_ARG, "bad precision");
     if (reps < 1) reps = 5;
     hipStream_t s = (hipStream_t)stream;
+    // the tables of all column candidates and of all block ones (built by the
+    // first of them)
+    struct Tables : sem::FusedPlan {
+        ~Tables() { sem::fused_plan_free(*this); }
+    } cols, blks;
+    if ((rc = sem::fused_plan_build(M->host, SEM_LAYOUT_COLUMNS, 0, cols, true)) != SEM_OK)
+        return fail(rc, "could not build the fused-stage tables");
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
-    // candidates: single columns in chunks of 1, 2, 4, 8 layers, in FP64 in
-    // each thread order (float runs the natural order in any); column
-    // blocks in 1, 2, 4, ... vertical segments (distinct segment lengths)
+    // candidates: where the owner kernel runs, the default layout; single
+    // columns in chunks of 1, 2, 4, 8 layers, in FP64 in each thread order
+    // (float runs the natural order in any); column blocks in 1, 2, 4, ...
+    // vertical segments (distinct segment lengths)
     std::vector<std::pair<int, int>> cand;
-    // where the owner kernel runs, chunks and orders concern the columns of
-    // the irregular nodes alone: one candidate, the default
-    const bool own = sem::own_used(M->d, prec);
+    const bool own = cols.own && sem::own_used(M->d, prec);
     if (own) cand.push_back({SEM_LAYOUT_COLUMNS, 0});
-    for (int lpc = 1; lpc <= 16 && !own; lpc *= 2)
+    for (int lpc = 1; lpc <= 16; lpc *= 2)
         if (sem::fused_lpc_supported(M->host.N, lpc) && lpc <= 2 * M->host.n_z) {
             cand.push_back({SEM_LAYOUT_COLUMNS, lpc});
             if (prec == SEM_FP64) {
@@ -1407,14 +1415,18 @@ static int sem_stage_autotune_impl(sem_mesh* M, const double* qn, const double* 
             cand.push_back({SEM_LAYOUT_BLOCKS, S});
         }
     }
-    int best = -1;
-    float best_t = 0.0f;
+    int best = -1, best_named = -1;                        // (of the column candidates that name a chunk)
+    float best_t = 0.0f, best_named_t = 0.0f;
+    bool blocks = true;
     for (size_t ci = 0; ci < cand.size(); ++ci) {
-        sem::FusedPlan P;
-        if (sem::fused_plan_build(M->host, cand[ci].first, cand[ci].second, P, own) != SEM_OK) {
-            sem::fused_plan_free(P);
-            continue;
-        }
+        const auto [layout, param] = cand[ci];
+        const bool blk = layout == SEM_LAYOUT_BLOCKS, named = !blk && param > 0;
+        if (blk && blks.allocs.empty() && blocks)
+            blocks = sem::fused_plan_build(M->host, layout, param, blks, false) == SEM_OK;
+        if (blk && !blocks) continue;
+        sem::FusedPlan P = blk ? blks : cols;              // (the tables stay theirs)
+        if (sem::fused_plan_set(M->host, layout, param, P) != SEM_OK) continue;
+        if (named) P.own = false;
         // warm-up, then timed repetitions (the stage coefficients do not
         // change the work; qout is scratch here)
         rc = sem::fused_stage_launch(M->d, P, 0.5, 0.5, 1e-3, qn, qs, qout, prec, s);
@@ -1429,14 +1441,31 @@ static int sem_stage_autotune_impl(sem_mesh* M, const double* qn, const double* 
             hipEventElapsedTime(&ms, e0, e1) == hipSuccess) {
             ms /= float(reps);
             if (best < 0 || ms < best_t) { best = int(ci); best_t = ms; }
+            if (named && (best_named < 0 || ms < best_named_t)) { best_named = int(ci); best_named_t = ms; }
         }
         (void)hipStreamSynchronize(s);
-        sem::fused_plan_free(P);
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (best < 0) return fail(SEM_ERR_HIP, "autotuning found no working configuration");
-    if ((rc = sem_stage_set_layout(M, cand[best].first, cand[best].second)) != SEM_OK) return rc;
+    // the plan of the fastest; a default one keeps the fastest order and chunk
+    // for the stages that the owner kernel does not take, and a plan tuned for
+    // those keeps the owner kernel for the others
+    Tables& T = cand[best].first == SEM_LAYOUT_BLOCKS ? blks : cols;
+    const bool default_wins = sem::fused_plan_owner(cand[best].first, cand[best].second);
+    if (default_wins && best_named >= 0)
+        (void)sem::fused_plan_set(M->host, cand[best_named].first, cand[best_named].second, T);
+    else if ((rc = sem::fused_plan_set(M->host, cand[best].first, cand[best].second, T)) != SEM_OK)
+        return fail(rc, "could not build the fused-stage tables");
+    if (default_wins) {
+        T.layout = SEM_LAYOUT_COLUMNS;
+        T.by_default = true;
+    } else if (own) {
+        T.own = false;
+    }
+    HIPCHK(hipDeviceSynchronize());
+    std::swap(M->fused, static_cast<sem::FusedPlan&>(T));
+    ++M->epoch;
     if (best_lpc) *best_lpc = M->fused.t.layers_per_chunk;
     if (best_ms) *best_ms = best_t;
     return SEM_OK;

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "devmesh.h"
+#include "sem.h"
 
 namespace sem {
 
@@ -110,6 +111,7 @@ struct FusedPlan {
     TailTables tail{};                    // column layout with side columns
     bool has_tail = false;
     bool own = false;                     // tables of the owner kernel (own_used: whether a stage runs it)
+    bool by_default = false;              // column layout at param = 0
     OwnTables ot{};
     FusedTables to{};                     // its side columns (one launch) and their tail
     TailTables own_tail{};
@@ -127,7 +129,13 @@ struct FusedPlan {
 // chunk (0 = default);
 // SEM_LAYOUT_BLOCKS: param = vertical segments (0 = default).  owner: with the
 // owner kernel's tables where it applies.
-int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& plan, bool owner = true);
+int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& plan, bool owner);
+// Another layout of the same kind, or another param, on the tables that a plan
+// has (none of them depends on these).
+int fused_plan_set(const HostMesh& H, int layout, int param, FusedPlan& plan);
+// Whether stages of a layout take the owner kernel where it applies: a program
+// that names a thread order or a chunk gets the coloured launches it names.
+inline bool fused_plan_owner(int layout, int param) { return layout == SEM_LAYOUT_COLUMNS && param == 0; }
 void fused_plan_free(FusedPlan& plan);
 bool fused_lpc_supported(int N, int layers_per_chunk);
 // whether the split-element thread order applies (two or more layers per

@@ -1415,18 +1415,13 @@ struct Arena {
     }
 };
 
-int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owner, Arena& A) {
+bool column_layout(int layout) {
+    return layout == SEM_LAYOUT_COLUMNS || layout == SEM_LAYOUT_COLUMNS_KZ || layout == SEM_LAYOUT_COLUMNS_SPLIT;
+}
+
+int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A) {
     const int np2 = H.np1 * H.np1;
-    const bool columns = layout == SEM_LAYOUT_COLUMNS || layout == SEM_LAYOUT_COLUMNS_KZ ||
-                         layout == SEM_LAYOUT_COLUMNS_SPLIT;
-    int lpc = columns ? param : 0;
-    if (lpc < 1) {
-        // default: the deepest supported chunk of at most 512 threads
-        lpc = 1;
-        while (fused_lpc_supported(H.N, lpc * 2) && np2 * (2 * lpc * H.N + 1) <= 512) lpc *= 2;
-    }
-    if (!fused_lpc_supported(H.N, lpc)) return SEM_ERR_ARG;
-    if (layout == SEM_LAYOUT_COLUMNS_SPLIT && !fused_split_supported(H.N, lpc)) return SEM_ERR_ARG;
+    const bool columns = column_layout(layout);
     if (layout == SEM_LAYOUT_BLOCKS && !fused_blocks_supported(H)) return SEM_ERR_ARG;
     if (!columns && layout != SEM_LAYOUT_BLOCKS) return SEM_ERR_ARG;
     auto up = [&](const void* src, size_t bytes, void** dst) -> int {
@@ -1660,11 +1655,8 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
         if ((rc = up(first.data(), first.size(), &d)) != SEM_OK) return rc;
         P.t.first = static_cast<const uint8_t*>(d);
         P.t.n_color = n_color;
-        P.t.layers_per_chunk = lpc;
-        P.t.thread_order = layout == SEM_LAYOUT_COLUMNS_KZ ? 1 : layout == SEM_LAYOUT_COLUMNS_SPLIT ? 2 : 0;
         P.color_ptr_host = cptr;
     }
-    P.layout = columns ? layout : SEM_LAYOUT_COLUMNS;
     if (columns && owner && own_applies(H.N, H.n_col)) {
         // ---- owner kernel: the regular nodes and their owners.  Nodes inside
         // a column are regular (a coarse face has none), so that only the
@@ -1874,18 +1866,6 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
         bptr[k + 1] = int32_t(border.size());
         sptr[k + 1] = int32_t(sorder.size());
     }
-    // vertical segments: by default enough for about 1024 workgroups per
-    // launch of the largest colour (two resident per CU on 256 CUs, both
-    // parities), at least one layer each
-    int S = param;
-    if (S < 1) {
-        int nbmax = 1;
-        for (int k = 0; k < n_color; ++k) nbmax = std::max(nbmax, bptr[k + 1] - bptr[k]);
-        S = 1;
-        while (S < H.n_z && nbmax * S < 1024) S *= 2;
-    }
-    S = std::min(S, H.n_z);
-    const int Ls = (H.n_z + S - 1) / S;
     if ((rc = up(border.data(), border.size() * 4, &d)) != SEM_OK) return rc;
     P.bt.order = static_cast<const int32_t*>(d);
     if ((rc = up(pos_g.data(), pos_g.size() * 4, &d)) != SEM_OK) return rc;
@@ -1895,8 +1875,6 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
     if ((rc = up(blk_col.data(), blk_col.size() * 4, &d)) != SEM_OK) return rc;
     P.bt.blk_col = static_cast<const int32_t*>(d);
     P.bt.cH = P.t.cH;
-    P.bt.Ls = Ls;
-    P.bt.n_seg = (H.n_z + Ls - 1) / Ls;
     P.bt.fsh = P.t.fsh;
     P.ts = P.t;
     // the columns in no block read the mesh's own position map and rows (the
@@ -1920,20 +1898,52 @@ int plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owne
     P.ts.first = static_cast<const uint8_t*>(d);
     P.ts.color_ptr = nullptr;
     P.ts.n_color = n_color;
-    P.ts.thread_order = 0;
     P.blk_ptr_host = bptr;
     P.single_ptr_host = sptr;
     P.n_unit_color = n_color;
     P.blk_wrap = fused_blocks_wrap(H);
-    P.layout = SEM_LAYOUT_BLOCKS;
     return SEM_OK;
 }
 
 }  // namespace
 
+int fused_plan_set(const HostMesh& H, int layout, int param, FusedPlan& P) {
+    const bool columns = column_layout(layout);
+    int lpc = columns ? param : 0;
+    if (lpc < 1) {
+        // default: the deepest supported chunk of at most 512 threads
+        lpc = 1;
+        while (fused_lpc_supported(H.N, lpc * 2) && H.np1 * H.np1 * (2 * lpc * H.N + 1) <= 512) lpc *= 2;
+    }
+    if (!fused_lpc_supported(H.N, lpc)) return SEM_ERR_ARG;
+    if (layout == SEM_LAYOUT_COLUMNS_SPLIT && !fused_split_supported(H.N, lpc)) return SEM_ERR_ARG;
+    P.layout = layout;
+    P.by_default = fused_plan_owner(layout, param);
+    P.t.layers_per_chunk = lpc;
+    P.t.thread_order = layout == SEM_LAYOUT_COLUMNS_KZ ? 1 : layout == SEM_LAYOUT_COLUMNS_SPLIT ? 2 : 0;
+    if (columns) return SEM_OK;
+    P.ts.layers_per_chunk = lpc;
+    P.ts.thread_order = 0;
+    // vertical segments: by default enough for about 1024 workgroups per
+    // launch of the largest colour (two resident per CU on 256 CUs, both
+    // parities), at least one layer each
+    int S = param;
+    if (S < 1) {
+        int nbmax = 1;
+        for (int k = 0; k < P.n_unit_color; ++k) nbmax = std::max(nbmax, P.blk_ptr_host[k + 1] - P.blk_ptr_host[k]);
+        S = 1;
+        while (S < H.n_z && nbmax * S < 1024) S *= 2;
+    }
+    S = std::min(S, H.n_z);
+    P.bt.Ls = (H.n_z + S - 1) / S;
+    P.bt.n_seg = (H.n_z + P.bt.Ls - 1) / P.bt.Ls;
+    return SEM_OK;
+}
+
 int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owner) {
     Arena A(P);
-    const int rc = plan_build(H, layout, param, P, owner, A);
+    int rc = plan_build(H, layout, P, owner, A);
+    if (rc == SEM_OK) rc = fused_plan_set(H, layout, param, P);
     return rc != SEM_OK ? rc : A.flush();
 }
 
