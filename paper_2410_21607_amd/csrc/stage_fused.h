@@ -150,14 +150,14 @@ bool fused_blocks_wrap(const HostMesh& H);
 // kernel (FP64, box elements, column layout) instead of a pre-pass.
 bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& plan, int precision);
 
-// The owner kernel: whether it has an instance of order N; whether it is the
-// faster one for a mesh of n_col columns (its plans then hold its tables);
-// whether a mesh is within its limits (32-bit offsets of the state, the level
-// table in LDS); whether a column-layout stage runs it; its launch over the
-// plan's regular nodes.
+// The owner kernel: whether it has an instance of order N; whether a state is
+// within its limits (32-bit offsets, the level table in LDS); whether plans of a
+// mesh hold its tables (an instance, the limits, and where it is the faster
+// one); whether a default-layout stage on such a mesh takes it; its launch over
+// the plan's regular nodes.
 bool own_supported(int N);
-bool own_applies(int N, int n_col);
-bool own_fits(const DevMesh& m);
+bool own_fits(int64_t n_h, int ldz, int nzn);
+bool own_applies(const HostMesh& H);
 bool own_used(const DevMesh& m, int precision);
 int own_launch(const DevMesh& m, const OwnTables& ot, double a, double b, double c, const double* qn,
                const double* qs, double* qout, hipStream_t stream);

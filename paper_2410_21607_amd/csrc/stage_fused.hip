@@ -46,6 +46,7 @@
 #include <string>
 #include <type_traits>
 
+#include "host_par.h"
 #include "mesh_build.h"
 #include "nodeval.h"
 #include "sem.h"
@@ -1341,19 +1342,26 @@ std::vector<int32_t> colour_units(const HostMesh& H, const std::vector<int32_t>&
     const int np2 = H.np1 * H.np1;
     std::vector<std::vector<int32_t>> adj(static_cast<size_t>(n_unit));
     auto link = [&](const std::vector<int32_t>& ptr, const std::vector<int32_t>& slot, int64_t n) {
-        for (int64_t x = 0; x < n; ++x)
-            for (int32_t q = ptr[x]; q < ptr[x + 1]; ++q)
+        for (int64_t x = 0; x < n; ++x) {
+            if (ptr[x + 1] - ptr[x] < 2) continue;         // (most nodes)
+            for (int32_t q = ptr[x]; q < ptr[x + 1]; ++q) {
+                const int32_t u1 = unit_of_col[slot[q] / np2];
+                std::vector<int32_t>& a = adj[u1];
                 for (int32_t r = ptr[x]; r < ptr[x + 1]; ++r) {
-                    const int32_t u1 = unit_of_col[slot[q] / np2], u2 = unit_of_col[slot[r] / np2];
-                    if (u1 != u2) adj[u1].push_back(u2);
+                    const int32_t u2 = unit_of_col[slot[r] / np2];
+                    // (the nodes of a side follow each other)
+                    if (u1 != u2 && (a.empty() || a.back() != u2)) a.push_back(u2);
                 }
+            }
+        }
     };
     link(H.asm_ptr, H.asm_slot, H.n_h);
     link(H.asmH_ptr, H.asmH_slot, H.n_hh);
     std::vector<int32_t> color(size_t(n_unit), -1);
+    std::vector<char> used;
     n_color = 0;
     for (int32_t u : unit_order) {
-        std::vector<char> used(size_t(n_color) + 1, 0);
+        used.assign(size_t(n_color) + 1, 0);
         for (int32_t o : adj[u])
             if (color[o] >= 0) used[color[o]] = 1;
         int k = 0;
@@ -1374,43 +1382,52 @@ uint64_t spread_bits(uint64_t x) {
     return (x | x << 1) & 0x5555555555555555u;
 }
 
-// The plan's tables in a few allocations, each filled by one copy: some 40
-// small ones take as long as building them (two-level mesh over 64 x 64
-// columns at N = 4: 4.4 ms for the tables of a layout, 3.1 so).
+// Tables of a plan on their way to the GPU, in a few allocations, each filled
+// by one copy: some 40 small ones take as long as building them (two-level mesh
+// over 64 x 64 columns at N = 4: 4.4 ms for the tables of a layout, 3.1 so).
+// put() needs no GPU, so that parts of a plan can be built on threads of their own.
 struct Arena {
     static constexpr size_t CHUNK = size_t(2) << 20;
-    FusedPlan& P;
-    std::unique_ptr<char[]> host;
-    char* dev = nullptr;
-    size_t used = 0, cap = 0;
-    explicit Arena(FusedPlan& plan) : P(plan) {}
-    int flush() {
-        const bool ok = used == 0 || hipMemcpy(dev, host.get(), used, hipMemcpyHostToDevice) == hipSuccess;
-        used = cap = 0;
-        return ok ? SEM_OK : SEM_ERR_HIP;
-    }
-    int alloc(size_t bytes, void** dst) {
-        if (hipMalloc(dst, bytes) != hipSuccess) return SEM_ERR_HIP;
-        P.allocs.push_back(*dst);
-        P.bytes += int64_t(bytes);
-        return SEM_OK;
-    }
-    // device address of a table; its contents are there after flush()
-    int put(const void* src, size_t bytes, void** dst) {
-        size_t at = (used + 255) / 256 * 256;
-        if (at + bytes > cap) {
-            if (const int rc = flush(); rc != SEM_OK) return rc;
-            const size_t size = std::max(bytes, CHUNK);
-            host.reset(new char[size]);
-            void* d = nullptr;
-            if (const int rc = alloc(size, &d); rc != SEM_OK) return rc;
-            dev = static_cast<char*>(d);
-            cap = size;
+    struct Chunk {
+        std::unique_ptr<char[]> host;
+        size_t used, cap;
+    };
+    struct Table {
+        void* field;                   // the plan's pointer to it
+        size_t chunk, at;
+    };
+    std::vector<Chunk> chunks;
+    std::vector<Table> tables;
+    // *field holds the table's device address after upload()
+    template <typename T>
+    void put(const std::vector<T>& v, const T** field) {
+        // an empty table still gets 8 (never read) bytes
+        const size_t bytes = v.size() * sizeof(T), room = std::max<size_t>(bytes, 8);
+        size_t at = chunks.empty() ? 0 : (chunks.back().used + 255) / 256 * 256;
+        if (chunks.empty() || at + room > chunks.back().cap) {
+            const size_t cap = std::max(room, CHUNK);
+            chunks.push_back({std::unique_ptr<char[]>(new char[cap]), 0, cap});
             at = 0;
         }
-        std::memcpy(host.get() + at, src, bytes);
-        used = at + bytes;
-        *dst = dev + at;
+        if (bytes) std::memcpy(chunks.back().host.get() + at, v.data(), bytes);
+        chunks.back().used = at + room;
+        tables.push_back({field, chunks.size() - 1, at});
+    }
+    int upload(FusedPlan& P) {
+        std::vector<char*> dev;
+        P.allocs.reserve(P.allocs.size() + chunks.size());
+        for (const Chunk& c : chunks) {
+            void* d = nullptr;
+            if (hipMalloc(&d, c.used) != hipSuccess) return SEM_ERR_HIP;
+            P.allocs.push_back(d);
+            P.bytes += int64_t(c.used);
+            if (hipMemcpy(d, c.host.get(), c.used, hipMemcpyHostToDevice) != hipSuccess) return SEM_ERR_HIP;
+            dev.push_back(static_cast<char*>(d));
+        }
+        for (const Table& t : tables) {
+            const void* p = dev[t.chunk] + t.at;
+            std::memcpy(t.field, &p, sizeof p);
+        }
         return SEM_OK;
     }
 };
@@ -1419,16 +1436,11 @@ bool column_layout(int layout) {
     return layout == SEM_LAYOUT_COLUMNS || layout == SEM_LAYOUT_COLUMNS_KZ || layout == SEM_LAYOUT_COLUMNS_SPLIT;
 }
 
-int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A) {
+int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner) {
     const int np2 = H.np1 * H.np1;
     const bool columns = column_layout(layout);
     if (layout == SEM_LAYOUT_BLOCKS && !fused_blocks_supported(H)) return SEM_ERR_ARG;
     if (!columns && layout != SEM_LAYOUT_BLOCKS) return SEM_ERR_ARG;
-    auto up = [&](const void* src, size_t bytes, void** dst) -> int {
-        *dst = nullptr;
-        if (bytes == 0) return SEM_OK;
-        return src ? A.put(src, bytes, dst) : A.alloc(bytes, dst);
-    };
     // first contributor of every node: the lowest colour among its units
     auto mark_first = [&](const std::vector<int32_t>& unit_of_col, const std::vector<int32_t>& color,
                           auto&& set_first) {
@@ -1444,23 +1456,13 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A
         mark(H.asm_ptr, H.asm_slot, H.n_h);
         mark(H.asmH_ptr, H.asmH_slot, H.n_hh);
     };
-    auto upv = [&](const auto& v, auto** dst) -> int {
-        void* pd = nullptr;
-        const size_t bytes = v.size() * sizeof(v[0]);
-        // an empty table still gets a (never read) 8-byte allocation
-        int r2 = up(bytes ? static_cast<const void*>(v.data()) : nullptr,
-                    std::max<size_t>(bytes, 8), &pd);
-        *dst = static_cast<std::remove_pointer_t<decltype(dst)>>(pd);
-        return r2;
-    };
     // Position map, interpolation rows and contribution buffer of a column
     // launch in which the columns `side_cols` (side_of_col: their index, else
     // -1) only write their own slots, and the tail that finishes the nodes of
     // those columns and the parents of hanging points, except the ones that
     // others finish (`done`, by node).
     auto side_tables = [&](const std::vector<int32_t>& side_cols, const std::vector<int32_t>& side_of_col,
-                           const std::vector<char>& done, FusedTables& t, TailTables& T) -> int {
-        int rc;
+                           const std::vector<char>& done, FusedTables& t, TailTables& T, Arena& A) {
         // positions of side columns become pseudo hanging points n_hh + k (N+1)^2 + pos
         const int64_t n_pseudo = int64_t(side_cols.size()) * np2;
         auto pseudo = [&](int32_t slot) {
@@ -1488,11 +1490,11 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A
                 hptr_x.push_back(int32_t(hsrc_x.size()));
                 gmap_x[slot] = -(pseudo(slot) + 1);
             }
-        if ((rc = upv(gmap_x, &t.gmap)) != SEM_OK) return rc;
-        if ((rc = upv(hptr_x, &t.hang_ptr)) != SEM_OK) return rc;
-        if ((rc = upv(hsrc_x, &t.hang_src)) != SEM_OK) return rc;
-        if ((rc = upv(hw_x, &t.hang_w)) != SEM_OK) return rc;
-        if ((rc = upv(hreal, &t.hreal)) != SEM_OK) return rc;
+        A.put(gmap_x, &t.gmap);
+        A.put(hptr_x, &t.hang_ptr);
+        A.put(hsrc_x, &t.hang_src);
+        A.put(hw_x, &t.hang_w);
+        A.put(hreal, &t.hreal);
         t.fsh = (H.n_hh + n_pseudo) * H.ldz;
         if (!side_cols.empty()) {
             // tail tables: unique nodes with side slots or Z^T rows
@@ -1562,21 +1564,18 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A
                 }
                 eptr.push_back(int32_t(erow.size()));
             }
-            if ((rc = upv(th, &T.h)) != SEM_OK) return rc;
-            if ((rc = upv(tfirst, &T.first)) != SEM_OK) return rc;
-            if ((rc = upv(eptr, &T.eptr)) != SEM_OK) return rc;
-            if ((rc = upv(erow, &T.erow)) != SEM_OK) return rc;
-            if ((rc = upv(ew, &T.ew)) != SEM_OK) return rc;
-            if ((rc = upv(estart, &T.estart)) != SEM_OK) return rc;
+            A.put(th, &T.h);
+            A.put(tfirst, &T.first);
+            A.put(eptr, &T.eptr);
+            A.put(erow, &T.erow);
+            A.put(ew, &T.ew);
+            A.put(estart, &T.estart);
             T.n = int(th.size());
             T.fsh = t.fsh;
         }
-        return SEM_OK;
     };
-    void* d;
-    int rc;
     // ---- column layout over every column (also the terrain path)
-    {
+    auto coloured = [&](Arena& A) {
         std::vector<int32_t> unit_of_col(static_cast<size_t>(H.n_col)), corder(static_cast<size_t>(H.n_col));
         for (int c = 0; c < H.n_col; ++c) unit_of_col[c] = corder[c] = c;
         int n_color = 0;
@@ -1645,22 +1644,18 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A
         });
         for (int32_t sc : side_cols)
             for (int pos = 0; pos < np2; ++pos) first[size_t(sc) * np2 + pos] = 1;
-        if ((rc = side_tables(side_cols, side_of_col, {}, P.t, P.tail)) != SEM_OK)
-            return rc;
+        side_tables(side_cols, side_of_col, {}, P.t, P.tail, A);
         P.has_tail = !side_cols.empty();
-        if ((rc = up(order.data(), order.size() * 4, &d)) != SEM_OK) return rc;
-        P.t.col_order = static_cast<const int32_t*>(d);
-        if ((rc = up(cptr.data(), cptr.size() * 4, &d)) != SEM_OK) return rc;
-        P.t.color_ptr = static_cast<const int32_t*>(d);
-        if ((rc = up(first.data(), first.size(), &d)) != SEM_OK) return rc;
-        P.t.first = static_cast<const uint8_t*>(d);
+        A.put(order, &P.t.col_order);
+        A.put(cptr, &P.t.color_ptr);
+        A.put(first, &P.t.first);
         P.t.n_color = n_color;
         P.color_ptr_host = cptr;
-    }
-    if (columns && owner && own_applies(H.N, H.n_col)) {
-        // ---- owner kernel: the regular nodes and their owners.  Nodes inside
-        // a column are regular (a coarse face has none), so that only the
-        // positions on its sides are looked at.
+    };
+    // ---- owner kernel: the regular nodes and their owners.  Nodes inside a
+    // column are regular (a coarse face has none), so that only the positions
+    // on its sides are looked at.
+    auto owners = [&](Arena& A) {
         const int N = H.N, np1 = H.np1, HS = own_positions(N);
         // per node the columns that have it at (N, j) and (i, N), their number
         // and level, and which of (i, j), (N, j), (i, N), (N, N) it is in them
@@ -1771,24 +1766,23 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A
             omask.push_back(mask[cc]);
             ohang.push_back(lowest < 0 ? 1 : 0);
         }
-        if ((rc = upv(map, &P.ot.map)) != SEM_OK) return rc;
-        if ((rc = upv(sxy, &P.ot.sxy)) != SEM_OK) return rc;
-        if ((rc = upv(omask, &P.ot.mask)) != SEM_OK) return rc;
-        if ((rc = upv(ohang, &P.ot.hang)) != SEM_OK) return rc;
+        A.put(map, &P.ot.map);
+        A.put(sxy, &P.ot.sxy);
+        A.put(omask, &P.ot.mask);
+        A.put(ohang, &P.ot.hang);
         P.ot.n = int(own.size());
         P.n_side = int(side_cols.size());
         if (P.n_side > 0) {
-            if ((rc = side_tables(side_cols, side_of_col, regular, P.to, P.own_tail)) != SEM_OK)
-                return rc;
+            side_tables(side_cols, side_of_col, regular, P.to, P.own_tail, A);
             std::vector<uint8_t> first(H.gmap.size(), 1);   // every slot has one writer
-            if ((rc = upv(first, &P.to.first)) != SEM_OK) return rc;
+            A.put(first, &P.to.first);
             // columns with the most hanging positions first, as above
             std::vector<int32_t> n_hang(static_cast<size_t>(H.n_col), 0);
             for (int32_t sc : side_cols)
                 for (int pos = 0; pos < np2; ++pos) n_hang[sc] += H.gmap[size_t(sc) * np2 + pos] < 0;
             std::stable_sort(side_cols.begin(), side_cols.end(),
                              [&](int32_t x, int32_t y) { return n_hang[x] > n_hang[y]; });
-            if ((rc = upv(side_cols, &P.to.col_order)) != SEM_OK) return rc;
+            A.put(side_cols, &P.to.col_order);
             P.to.n_color = 1;
             // a few hundred columns, paced by the latency of their chunks: the
             // deepest chunk, natural order.  us per stage with 2, 4 and 8
@@ -1801,10 +1795,25 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A
             P.to.thread_order = 1;
         }
         P.own = true;
+    };
+    {
+        // each on a thread, but for meshes whose tables take less time than
+        // starting one
+        Arena A[2];
+        const int parts = columns && owner && own_applies(H) ? 2 : 1;
+        parallel_ranges(size_t(parts), std::min(parts, host_threads(8 * H.gmap.size())), [&](size_t b, size_t e, int) {
+            for (size_t part = b; part < e; ++part) part == 0 ? coloured(A[0]) : owners(A[1]);
+        });
+        for (Arena& x : A)
+            if (const int rc = x.upload(P); rc != SEM_OK) return rc;
     }
     // one buffer of contributions: a stage runs the coloured launches or the
     // owner kernel's, and stages of one handle do not overlap
-    if ((rc = up(nullptr, std::max<size_t>(size_t(NF) * std::max(P.t.fsh, P.to.fsh) * 8, 8), &d)) != SEM_OK) return rc;
+    const size_t cbytes = std::max<size_t>(size_t(NF) * std::max(P.t.fsh, P.to.fsh) * 8, 8);
+    void* d = nullptr;
+    if (hipMalloc(&d, cbytes) != hipSuccess) return SEM_ERR_HIP;
+    P.allocs.push_back(d);
+    P.bytes += int64_t(cbytes);
     P.t.cH = P.to.cH = static_cast<double*>(d);
     P.tail.cH = P.own_tail.cH = P.t.cH;
     if (columns) return SEM_OK;
@@ -1866,43 +1875,31 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner, Arena& A
         bptr[k + 1] = int32_t(border.size());
         sptr[k + 1] = int32_t(sorder.size());
     }
-    if ((rc = up(border.data(), border.size() * 4, &d)) != SEM_OK) return rc;
-    P.bt.order = static_cast<const int32_t*>(d);
-    if ((rc = up(pos_g.data(), pos_g.size() * 4, &d)) != SEM_OK) return rc;
-    P.bt.pos_g = static_cast<const int32_t*>(d);
-    if ((rc = up(pos_first.data(), pos_first.size(), &d)) != SEM_OK) return rc;
-    P.bt.pos_first = static_cast<const uint8_t*>(d);
-    if ((rc = up(blk_col.data(), blk_col.size() * 4, &d)) != SEM_OK) return rc;
-    P.bt.blk_col = static_cast<const int32_t*>(d);
+    Arena A;
+    A.put(border, &P.bt.order);
+    A.put(pos_g, &P.bt.pos_g);
+    A.put(pos_first, &P.bt.pos_first);
+    A.put(blk_col, &P.bt.blk_col);
     P.bt.cH = P.t.cH;
     P.bt.fsh = P.t.fsh;
     P.ts = P.t;
     // the columns in no block read the mesh's own position map and rows (the
     // column layout's pseudo hanging points belong to its side columns only)
-    if ((rc = up(H.gmap.data(), H.gmap.size() * 4, &d)) != SEM_OK) return rc;
-    P.ts.gmap = static_cast<const int32_t*>(d);
+    A.put(H.gmap, &P.ts.gmap);
     if (H.n_hh > 0) {
-        if ((rc = up(H.hang_ptr.data(), H.hang_ptr.size() * 4, &d)) != SEM_OK) return rc;
-        P.ts.hang_ptr = static_cast<const int32_t*>(d);
-        if ((rc = up(H.hang_src.data(), H.hang_src.size() * 4, &d)) != SEM_OK) return rc;
-        P.ts.hang_src = static_cast<const int32_t*>(d);
-        if ((rc = up(H.hang_w.data(), H.hang_w.size() * 8, &d)) != SEM_OK) return rc;
-        P.ts.hang_w = static_cast<const double*>(d);
+        A.put(H.hang_ptr, &P.ts.hang_ptr);
+        A.put(H.hang_src, &P.ts.hang_src);
+        A.put(H.hang_w, &P.ts.hang_w);
     }
-    P.ts.col_order = nullptr;
-    if (!sorder.empty()) {
-        if ((rc = up(sorder.data(), sorder.size() * 4, &d)) != SEM_OK) return rc;
-        P.ts.col_order = static_cast<const int32_t*>(d);
-    }
-    if ((rc = up(first_s.data(), first_s.size(), &d)) != SEM_OK) return rc;
-    P.ts.first = static_cast<const uint8_t*>(d);
+    A.put(sorder, &P.ts.col_order);
+    A.put(first_s, &P.ts.first);
     P.ts.color_ptr = nullptr;
     P.ts.n_color = n_color;
     P.blk_ptr_host = bptr;
     P.single_ptr_host = sptr;
     P.n_unit_color = n_color;
     P.blk_wrap = fused_blocks_wrap(H);
-    return SEM_OK;
+    return A.upload(P);
 }
 
 }  // namespace
@@ -1941,10 +1938,8 @@ int fused_plan_set(const HostMesh& H, int layout, int param, FusedPlan& P) {
 }
 
 int fused_plan_build(const HostMesh& H, int layout, int param, FusedPlan& P, bool owner) {
-    Arena A(P);
-    int rc = plan_build(H, layout, P, owner, A);
-    if (rc == SEM_OK) rc = fused_plan_set(H, layout, param, P);
-    return rc != SEM_OK ? rc : A.flush();
+    const int rc = plan_build(H, layout, P, owner);
+    return rc != SEM_OK ? rc : fused_plan_set(H, layout, param, P);
 }
 
 void fused_plan_free(FusedPlan& P) {
@@ -1998,11 +1993,12 @@ bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& P, int prec) {
 // column kernel: terrain and dissipation (their terms need more of a neighbour
 // than one line) and float (p' is rounded to float, and which way it goes must
 // not depend on the order of the sums: 8e-8 of the rms in w after one step).
-bool own_applies(int N, int n_col) { return own_supported(N) && (N != 7 || n_col <= 768); }
+bool own_applies(const HostMesh& H) {
+    return own_supported(H.N) && own_fits(H.n_h, H.ldz, H.nzn) && (H.N != 7 || H.n_col <= 768);
+}
 
 bool own_used(const DevMesh& m, int prec) {
-    return prec == SEM_FP64 && own_applies(m.N, m.n_col) && own_fits(m) && !m.zs && !m.rx && m.cs == 0.0 &&
-           !m.sponge;
+    return prec == SEM_FP64 && !m.zs && !m.rx && m.cs == 0.0 && !m.sponge;
 }
 
 int fused_stage_launch(const DevMesh& m_in, const FusedPlan& P, double a, double b, double c,

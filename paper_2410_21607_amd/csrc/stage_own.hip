@@ -507,9 +507,7 @@ bool own_supported(int N) {
     }
 }
 
-bool own_fits(const DevMesh& m) {
-    return int64_t(NF) * m.n_h * m.ldz * 8 < (int64_t(1) << 31) && m.nzn <= 512;
-}
+bool own_fits(int64_t n_h, int ldz, int nzn) { return NF * n_h * ldz * 8 < (int64_t(1) << 31) && nzn <= 512; }
 
 int own_launch(const DevMesh& m, const OwnTables& ot, double a, double b, double c, const double* qn,
                const double* qs, double* qo, hipStream_t s) {
