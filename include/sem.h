@@ -273,10 +273,10 @@ int sem_stage_update(const sem_mesh *mesh, double a, double b, double c,
  * right-hand side (scatter, element RHS, assembly, gather, finalize, lid rule)
  * evaluated without storing element-local data.  In the default layout an FP64
  * stage on box elements without dissipation (N >= 2, within 2 GiB of state and
- * 512 levels; N = 7 up to 768 columns) computes every node whose columns have one level
- * and surround it in one launch, by the one column that owns it; the columns
- * of the other nodes and the pass that sums theirs are two more launches.
- * Everywhere else work units (columns, or
+ * 512 levels; N = 7 up to 768 columns, 512 of one layer) computes every node
+ * whose columns have one level and surround it in one launch, by the one column
+ * that owns it; the columns of the other nodes and the pass that sums theirs
+ * are two more launches.  Everywhere else work units (columns, or
  * 2 x 2 column blocks: sem_stage_set_layout) are coloured so that units of
  * one colour share no node; the launches of one colour cover the units of
  * every refinement level of that colour (a workgroup marches up one column

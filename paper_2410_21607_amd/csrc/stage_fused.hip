@@ -1976,27 +1976,36 @@ bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& P, int prec) {
     return (m.cs > 0.0 || m.sponge) && !m.zs && prec == SEM_FP64 && !runs_blocks(m, P);
 }
 
-// The owner kernel takes over where it has an instance (N >= 2).  us per stage,
-// column kernel at its best chunk and owner kernel, by N:
-//   N  elements        col  own     elements       col  own
-//   2  24 x 24 x 16     31   13     64 x 64 x 16    54   38
-//   3  7 x 6 x 5        35    9     64 x 64 x 16   134   97
-//   4  8 x 8 x 4        27   12     64 x 64 x 16   230  172
-//   5  37 x 29 x 5      86   75     48 x 48 x 16   394  281
-//   6  20 x 20 x 6      81   49     40 x 40 x 12   317  317
-//   7  10 x 10 x 8     144   43     40 x 40 x 12   479  490
-//   8  12 x 12 x 8     204   62     36 x 36 x 8    465  379
+// Default stages take the owner kernel where it has an instance (N >= 2).  us
+// per stage, column kernel at its default chunk, at its best chunk and order, and
+// owner kernel (smooth states, uniform periodic meshes, 256 CUs), by N:
+//   N  elements       default  best  own     elements       default  best  own
+//   2  64 x 64 x 16        52    51   36     160 x 160 x 2      130    85  110
+//   3  64 x 64 x 16       133   123   97     160 x 160 x 2      347   153  311
+//   4  64 x 64 x 16       251   230  178     160 x 160 x 1      390   247  336
+//   5  64 x 64 x 8        300   268  281     100 x 100 x 1      215   165  170
+//   6  64 x 64 x 8        601   479  534     80 x 80 x 4        449   428  465
+//   7  24 x 32 x 16       347   290  285     24 x 32 x 2         53    49   45
+//   8  48 x 48 x 12      1047  1012  841     64 x 64 x 1        215   215  214
+// A mesh that nothing was tuned for gains by it (at N = 6 and 6,400 columns and
+// more of three or four layers it loses up to 5 %).  Where few layers leave its
+// chunk mostly idle a named chunk or order can be twice as fast: the autotuner
+// times both.
 // At N = 7 the state of more columns than the L2s hold at once is read more
 // than once (rows of odd length: a line has parts of two chunks), and the rule
-// draws the line at three columns per CU: 24 x 24 x 8 160 against 129, 28 x 28
-// x 8 180 against 177, 64 x 64 x 8 and a level 960 against 1035.  Left to the
-// column kernel: terrain and dissipation (their terms need more of a neighbour
-// than one line) and float (p' is rounded to float, and which way it goes must
-// not depend on the order of the sums: 8e-8 of the rms in w after one step).
+// draws the line at 768 columns, three per CU: 24 x 24 x 8 160 (default) against
+// 129, 28 x 28 x 8 180 against 177 (the crossover is not far above), 64 x 64 x 8
+// and a level 960 against 1035.  One layer fills half of its chunk there, and a
+// third round of workgroups is too many: 16 x 32 columns 32 against 29, 24 x 24
+// 33 against 41, 24 x 32 34 against 42.
 bool own_applies(const HostMesh& H) {
-    return own_supported(H.N) && own_fits(H.n_h, H.ldz, H.nzn) && (H.N != 7 || H.n_col <= 768);
+    return own_supported(H.N) && own_fits(H.n_h, H.ldz, H.nzn) &&
+           (H.N != 7 || H.n_col <= (H.n_z == 1 ? 512 : 768));
 }
 
+// Left to the column kernel: terrain and dissipation (no owner instance has
+// their terms) and float (p' is rounded to float, and which way it goes must
+// not depend on the order of the sums: 8e-8 of the rms in w after one step).
 bool own_used(const DevMesh& m, int prec) {
     return prec == SEM_FP64 && !m.zs && !m.rx && m.cs == 0.0 && !m.sponge;
 }

@@ -487,9 +487,10 @@ k_stage_own(DevMesh m, OwnTables ot, double a, double b, double c, const double*
     }
 }
 
-// (order, layers per chunk) instances: chunks of about 16 levels, two 128-byte
-// lines of a row; fewer where the threads would leave room for one workgroup
-// per CU.  us per stage with other chunks: N = 3 (64 x 64 x 16 elements) 4: 102,
+// (order, layers per chunk) instances, the fastest that was measured of each
+// order: up to N = 4 chunks of 16 or 24 levels, at N = 5 and 6 of 10 and 6, which
+// leave three workgroups per CU as N = 3 and 4 have; N = 7 and 8 have one (704 and
+// 512 threads of about 150 registers).  us per stage with other chunks: N = 3 (64 x 64 x 16 elements) 4: 102,
 // 8: 97; N = 4 8: 246, 4: 181; N = 5 (48 x 48 x 16) 1: 416, 2: 281, 4: 298;
 // N = 6 (40 x 40 x 12) 1: 317, 2: 327; N = 7 (28 x 28 x 8) 1: 231, 2: 177: a
 // layer's 56 bytes of a row keep every line waiting in the L2 for the next

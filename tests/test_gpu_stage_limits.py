@@ -1,5 +1,5 @@
 """Both sides of the owner kernel's limits: 512 levels (its level table in LDS),
-2 GiB of state (32-bit offsets), 768 columns at N = 7.  Below, a default stage
+2 GiB of state (32-bit offsets), 768 columns at N = 7 (512 of one layer).  Below, a default stage
 runs it (reported layout (0, 0)); above, the coloured launches, to the bit of
 those named.  Against the oracle at the bar of every FP64 call, or against the
 named launches where the oracle would not fit."""
@@ -80,6 +80,6 @@ def test_state_bytes(nx, owner):
     _against_named(2, nx, 160, 255, owner)
 
 
-@pytest.mark.parametrize("nx,ny,owner", [(24, 32, True), (10, 77, False)])
-def test_columns_at_n7(nx, ny, owner):
-    _against_named(7, nx, ny, 2, owner)
+@pytest.mark.parametrize("nx,ny,nz,owner", [(24, 32, 2, True), (10, 77, 2, False), (16, 32, 1, True), (19, 27, 1, False)])
+def test_columns_at_n7(nx, ny, nz, owner):
+    _against_named(7, nx, ny, nz, owner)
