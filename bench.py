@@ -130,14 +130,28 @@ def column_instance(N, lpc, layout, fp64, diss_inline):
             f"{'true' if diss_inline else 'false'}, {order}>")
 
 
-def stage_instance(N, lpc, layout, fp64, diss_inline):
+def runs_owner(layout, param, fp64, dissipation):
+    """Whether a box-element stage runs the owner kernel: in FP64 without
+    dissipation, where the library reports the default layout (param 0: the
+    mesh is within that kernel's limits)."""
+    return fp64 and not dissipation and (layout, param) == (0, 0)
+
+
+def stage_instance(N, lpc, layout, param, fp64, dissipation):
     """Name (or its start) of the kernel instance that a box-element stage of a
-    uniform mesh runs: the owner kernel (template arguments: N + 1, its own
-    layers per chunk) in FP64 without dissipation at N >= 2, else the column
-    kernel; None for the block layout."""
-    if fp64 and not diss_inline and N >= 2 and layout in (0, 2, 3):
+    uniform periodic mesh runs: the owner kernel (template arguments: N + 1, its
+    own layers per chunk) or the column kernel; None for the block layout."""
+    if runs_owner(layout, param, fp64, dissipation):
         return f"k_stage_own<{N + 1}, "
-    return column_instance(N, lpc, layout, fp64, diss_inline)
+    return column_instance(N, lpc, layout, fp64, dissipation and fp64)
+
+
+def stage_launches(layout, param, fp64, dissipation, irregular):
+    """What the kernel time of a stage covers; irregular: hanging points or walls."""
+    if runs_owner(layout, param, fp64, dissipation):
+        return "fused stage (owner kernel" + (", side columns and their sums)" if irregular else ", one launch)")
+    unit = "block" if layout == 1 else "column"
+    return f"fused stage ({unit} passes" + (" + hanging pass)" if irregular else ")")
 
 
 def traffic_from_counters(fetch_csv, write_csv, workload=WORKLOAD, launches_per_stage=4, out_dir=None):
@@ -158,6 +172,9 @@ def traffic_from_counters(fetch_csv, write_csv, workload=WORKLOAD, launches_per_
     case = cases.get(workload)
     if int(np.asarray(case["columns"])[:, 0].max()) != 0:
         raise ValueError("the traffic summary covers uniform meshes only")
+    if not (case.get("periodic_x", True) and case.get("periodic_y", True)):
+        raise ValueError("the traffic summary covers periodic meshes only (walls: more launches than the owner "
+                         "kernel's make a stage)")
     info = api.sem_mesh_plan(case)[0]
     calib_bytes = 5 * info["n_h"] * info["ldz"] * 8
 
@@ -761,9 +778,11 @@ def main():
         for _ in range(5):
             torch.mul(src, 1.0, out=dst)
         torch.cuda.synchronize()
-    traffic = measured_traffic(args.workload, stage_instance(
-        case["N"], lpc, layout, prec == api.SEM_FP64,
-        bool(args.dissipation) and prec == api.SEM_FP64 and layout != api.SEM_LAYOUT_BLOCKS))
+    fp64, diss = prec == api.SEM_FP64, bool(args.dissipation)
+    owner = runs_owner(layout, layout_par, fp64, diss)
+    irregular = mesh.n_hang > 0 or not (case["periodic_x"] and case["periodic_y"])
+    instance = stage_instance(case["N"], lpc, layout, layout_par, fp64, diss)
+    traffic = measured_traffic(args.workload, instance) if instance and not irregular else None
     stages = 3 * n_steps
     res = {
         "metric": METRIC,
@@ -782,15 +801,15 @@ def main():
                    "n_dof": int(n_dof), "local_points": int(mesh.n_local),
                    "step": "one SSP-RK3 stage (timed as HIP-graph replays of whole RK3 steps)",
                    "graph": not args.no_graph,
-                   "layout": LAYOUT_NAMES[layout],
-                   "layers_per_chunk" if layout != api.SEM_LAYOUT_BLOCKS else "segments":
-                       lpc if layout != api.SEM_LAYOUT_BLOCKS else layout_par,
+                   "layout": "columns (owner kernel)" if owner else LAYOUT_NAMES[layout],
+                   **({} if owner else {"segments": layout_par} if layout == api.SEM_LAYOUT_BLOCKS
+                      else {"layers_per_chunk": lpc}),
                    "finite": ok,
                    "dissipation": args.dissipation or "off"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
-                     "kernel": "fused stage (column passes + hanging pass), per stage",
+                     "kernel": stage_launches(layout, layout_par, fp64, diss, irregular) + ", per stage",
                      "copy_kernel_GBps": copy_gbs,
                      "frac_of_copy": achieved / copy_gbs,
                      "avg_kernel_ms": float(durs.mean() * 1e3 / 3)},
