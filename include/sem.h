@@ -343,15 +343,15 @@ int sem_stage_get_tune(const sem_mesh *mesh, int *layers_per_chunk);
 int sem_stage_set_layout(sem_mesh *mesh, int layout, int param);
 int sem_stage_get_layout(const sem_mesh *mesh, int *layout, int *param);
 
-/* Autotuner: times every supported work layout on this mesh (the column
- * layout at each supported layers_per_chunk, in FP64 in each thread order,
- * the block layout at 1, 2, 4, ... vertical segments, and the default layout
- * where the owning columns' launch applies; reps fused stages
- * each, HIP events on `stream`, d_qout used as scratch),
- * keeps the fastest as sem_stage_set_layout would (a default layout with the
- * fastest order and chunk for the stages that need coloured launches; tuned for
- * such a stage, the others keep the owning columns' launch), and reports
- * it (*best_lpc = the column layout's layers per chunk, see
+/* Autotuner: times every supported work layout on this mesh (the default layout
+ * where the owning columns' launch applies, the column layout at each supported
+ * layers_per_chunk, in FP64 in each thread order, the block layout at 1, 2, 4,
+ * ... vertical segments; reps fused stages each, one of those that take half as
+ * long again as the fastest; HIP events on `stream`, d_qout used as scratch) and
+ * keeps the fastest as sem_stage_set_layout would (ties go to the default layout,
+ * which keeps the fastest order and chunk for the stages that need coloured
+ * launches; tuned for such a stage, the others keep the owning columns' launch).
+ * Reports it (*best_lpc = the column layout's layers per chunk, see
  * sem_stage_get_layout for the layout; *best_ms = mean stage time in ms;
  * either may be NULL).  Synchronises the stream. */
 int sem_stage_autotune(sem_mesh *mesh, const double *d_qn, const double *d_qs,

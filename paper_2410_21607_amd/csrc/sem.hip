@@ -1428,19 +1428,29 @@ static int sem_stage_autotune_impl(sem_mesh* M, const double* qn, const double* 
         if (sem::fused_plan_set(M->host, layout, param, P) != SEM_OK) continue;
         if (named) P.own = false;
         // warm-up, then timed repetitions (the stage coefficients do not
-        // change the work; qout is scratch here)
-        rc = sem::fused_stage_launch(M->d, P, 0.5, 0.5, 1e-3, qn, qs, qout, prec, s);
-        if (rc == SEM_OK) {
+        // change the work; qout is scratch here): one, and the others if it
+        // took no more than half as long again as the best
+        auto stages = [&](int n, float& ms) {
             (void)hipEventRecord(e0, s);
-            for (int r = 0; r < reps && rc == SEM_OK; ++r)
+            for (int r = 0; r < n && rc == SEM_OK; ++r)
                 rc = sem::fused_stage_launch(M->d, P, 0.5, 0.5, 1e-3, qn, qs, qout, prec, s);
             (void)hipEventRecord(e1, s);
-        }
+            const bool ok = rc == SEM_OK && hipEventSynchronize(e1) == hipSuccess &&
+                            hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
+            ms /= float(n);
+            return ok;
+        };
+        rc = sem::fused_stage_launch(M->d, P, 0.5, 0.5, 1e-3, qn, qs, qout, prec, s);
         float ms = 0.0f;
-        if (rc == SEM_OK && hipEventSynchronize(e1) == hipSuccess &&
-            hipEventElapsedTime(&ms, e0, e1) == hipSuccess) {
-            ms /= float(reps);
-            if (best < 0 || ms < best_t) { best = int(ci); best_t = ms; }
+        bool ok = rc == SEM_OK && stages(1, ms);
+        if (ok && reps > 1 && (best < 0 || ms <= 1.5f * best_t)) {
+            const float one = ms;
+            ok = stages(reps - 1, ms);
+            ms = (one + float(reps - 1) * ms) / float(reps);
+        }
+        if (ok) {
+            // (ties go to the default)
+            if (best < 0 || ms < (best == 0 && own ? 0.98f : 1.0f) * best_t) { best = int(ci); best_t = ms; }
             if (named && (best_named < 0 || ms < best_named_t)) { best_named = int(ci); best_named_t = ms; }
         }
         (void)hipStreamSynchronize(s);
