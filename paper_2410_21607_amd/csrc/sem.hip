@@ -77,29 +77,49 @@ __global__ void k_nc_gather(DevMesh m, const double* __restrict__ src, double* _
     }
 }
 
-// Element right-hand side: a workgroup takes up to rhs_layers stacked elements
-// of a column, a thread per local node.  Their rows are loaded once, kz
-// fastest, into tiles shared by the elements; (u, v), (w, theta') and (rho, p')
-// are read in pairs by the six sums of each direction.
-// Two-level mesh over 64 x 64 x 8 elements at N = 4: 140 us, 0.35 GB read and
-// written (147 with two layers per workgroup, 177 with one); 208 with a
+// Element right-hand side: a workgroup takes up to LZ stacked elements of a
+// column, a thread per local node.  Their rows are loaded once, kz fastest, into
+// tiles shared by the elements; (u, v), (w, theta') and (rho, p') are read in
+// pairs by the six sums of each direction.
+// Two-level mesh over 64 x 64 x 8 elements at N = 4: 132 us, 0.35 GB read and
+// written (145 with two layers per workgroup, 179 with one); 208 with a
 // workgroup per element, rows of 40 bytes and eight tiles read one by one.  The
 // rest is LDS reads (45 of 16 bytes per node) and latency at 4 waves per SIMD.
 template <int NP>
 constexpr int rhs_layers() {
-    return NP == 2 ? 16 : NP <= 4 ? 8 : NP == 5 ? 4 : NP == 6 ? 2 : 1;
+    return NP == 2 ? 16 : NP <= 5 ? 4 : 1;
 }
+// The instance (LZ = 1, 2, 4, 8, 16, at most rhs_layers) for n_z layers.  Threads
+// of empty layers hold their registers, and a chunk costs the same however full
+// it is: N = 3 and 4 take the largest LZ that divides n_z, two for odd numbers of
+// five and more.  us with 8, 4, 2 and 1 layers per workgroup at N = 3, 107 x 137 x
+// 2 elements and two levels 127, 75, 57, 81, 64 x 64 x 9 74, 49, 48, 57, 64 x 64 x
+// 16 84, 76, 79, 105; with 4, 2 and 1 at N = 4, 128 x 128 x 1 96, 66, 59, 100 x
+// 100 x 3 99, 92, 87, 64 x 64 x 5 83, 59, 68, x 9 130, 109, 115; with 2 and 1 at N
+// = 5, 64 x 64 x 8 290, 202.  Where a layer is 8 or 27 threads a chunk costs about
+// four layers (N = 1) or half a one (N = 2) more than its own: N = 1, 128 x 128 x
+// 16 with 16, 8 and 4 33, 38, 53, x 20 67, 51, 75, 160 x 160 x 5 32, 25, 43; N = 2,
+// 160 x 160 x 3 with 8, 4, 2 and 1 77, 52, 62, 77, 128 x 128 x 5 61, 67, 55, 78.
 template <int NP>
-constexpr int rhs_threads() {
-    return (rhs_layers<NP>() * NP * NP * NP + 63) / 64 * 64;
+int rhs_pick(int n_z) {
+    if constexpr (NP > 3) return std::min(rhs_layers<NP>(), n_z % 2 == 0 ? n_z & -n_z : n_z < 5 ? 1 : 2);
+    auto cost = [&](int lz) { return (n_z + lz - 1) / lz * (2 * lz + (NP == 2 ? 8 : 1)); };
+    int best = rhs_layers<NP>();
+    for (int lz = best; lz >= 1; lz /= 2)
+        if (cost(lz) < cost(best)) best = lz;
+    return best;
 }
-template <int NP, typename T>
-__global__ void __launch_bounds__(rhs_threads<NP>())
+template <int NP, int LZ>
+constexpr int rhs_threads() {
+    return (LZ * NP * NP * NP + 63) / 64 * 64;
+}
+template <int NP, int LZ, typename T>
+__global__ void __launch_bounds__((rhs_threads<NP, LZ>()))
 k_rhs(DevMesh m, const double* __restrict__ q, const double* __restrict__ hv,
       double* __restrict__ rE) {
     using T2 = std::conditional_t<sizeof(T) == 8, double2, float2>;
     constexpr int NP2 = NP * NP, NP3 = NP2 * NP, N = NP - 1;
-    constexpr int LZ = rhs_layers<NP>(), RT = rhs_threads<NP>(), ST = (LZ * N + 1) | 1;
+    constexpr int RT = rhs_threads<NP, LZ>(), ST = (LZ * N + 1) | 1;
     __shared__ T2 t_uv[NP2 * ST], t_wt[NP2 * ST], t_rp[NP2 * ST];
     __shared__ T t_r[NP2 * ST];           // rho'
     __shared__ T sD[NP2];
@@ -760,15 +780,21 @@ int grid_for(int64_t n, int block = 256) {
     return int(g);
 }
 
+template <int NP, typename T, int LZ = sem::rhs_layers<NP>()>
+void launch_rhs_k(const DevMesh& d, int lz, const double* q, const double* hv, double* rE, hipStream_t s) {
+    if constexpr (LZ > 1)
+        if (lz < LZ) return launch_rhs_k<NP, T, LZ / 2>(d, lz, q, hv, rE, s);
+    hipLaunchKernelGGL((sem::k_rhs<NP, LZ, T>), dim3(unsigned(d.n_col) * ((d.n_z + LZ - 1) / LZ)),
+                       dim3(sem::rhs_threads<NP, LZ>()), 0, s, d, q, hv, rE);
+}
+
 template <typename T>
 int launch_rhs_t(const sem_mesh* M, const double* q, const double* hv, double* rE, hipStream_t s) {
     const DevMesh& d = M->d;
     switch (d.N) {
 #define CASE(NN)                                                                             \
     case NN:                                                                                 \
-        hipLaunchKernelGGL((sem::k_rhs<NN + 1, T>),                                          \
-                           dim3(unsigned(d.n_col) * ((d.n_z + sem::rhs_layers<NN + 1>() - 1) / sem::rhs_layers<NN + 1>())), \
-                           dim3(sem::rhs_threads<NN + 1>()), 0, s, d, q, hv, rE);            \
+        launch_rhs_k<NN + 1, T>(d, sem::rhs_pick<NN + 1>(d.n_z), q, hv, rE, s);              \
         break;
         CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
 #undef CASE
