@@ -452,14 +452,17 @@ __device__ __forceinline__ void sum_local(const DevMesh& m, const double* __rest
     }
 }
 
-// from column rows (the dissipation pre-pass)
-__global__ void k_assemble(DevMesh m, const double* __restrict__ rE, double* __restrict__ acc) {
+// a thread per node and level: from column rows (the dissipation pre-pass), and
+// at N = 1 from the element layout too, whose lanes' doubles are 64 bytes apart
+// there (128 x 128 x 20 elements and a level 116 us, 177 by k_assemble_elem, whose
+// levels are all between two elements; from N = 2 that one is ahead)
+__global__ void k_assemble(DevMesh m, const double* __restrict__ rE, double* __restrict__ acc, bool col) {
     const int64_t n = int64_t(m.n_h) * m.nzn;
     for (int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; t < n;
          t += int64_t(gridDim.x) * blockDim.x) {
         const int h = int(t / m.nzn), kz = int(t % m.nzn);
         double s[NF];
-        sum_local(m, rE, m.asm_slot, m.asm_ptr[h], m.asm_ptr[h + 1], kz, s, true);
+        sum_local(m, rE, m.asm_slot, m.asm_ptr[h], m.asm_ptr[h + 1], kz, s, col);
         const int64_t o = int64_t(h) * m.ldz + kz, fs = int64_t(m.n_h) * m.ldz;
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[f * fs + o] = s[f];
@@ -482,7 +485,9 @@ __global__ void k_assemble_hang(DevMesh m, const double* __restrict__ rE, double
 // Assembly from the element layout of rE (position fastest): a workgroup takes
 // ASM_H horizontal nodes, a lane each, and ASM_K levels, a quarter per wave, so
 // that consecutive lanes read the consecutive positions of an element's plane
-// and a level's elements are the same for a whole wave; the sums (in
+// and a level's elements are the same for a whole wave (the quarter of what is
+// left in rows shorter than that: 107 x 137 x 2 elements at N = 3 73 to 65 us, 160
+// x 160 x 1 at N = 2 24 to 20); the sums (in
 // sum_local's order) are turned through LDS into rows, one 128-byte line per
 // node and field.
 // Bound by memory and the latency of the chain node - slots - planes: two-level
@@ -501,6 +506,7 @@ k_assemble_elem(DevMesh m, const double* __restrict__ rE, double* __restrict__ a
     const int n_kb = (m.nzn + ASM_K - 1) / ASM_K, G = gridDim.x, xcd = blockIdx.x & 7;
     const int b = xcd * (G >> 3) + min(xcd, G & 7) + (int(blockIdx.x) >> 3);
     const int h0 = b / n_kb * ASM_H, kz0 = b % n_kb * ASM_K;
+    const int nq = (min(ASM_K, m.nzn - kz0) + 3) / 4;      // levels per wave
     const int h = h0 + lane;
     double s[Q][NF];
 #pragma unroll
@@ -513,8 +519,8 @@ k_assemble_elem(DevMesh m, const double* __restrict__ rE, double* __restrict__ a
             const double* base = rE + int64_t(c) * m.n_z * np3 + (slot - c * np2);
 #pragma unroll
             for (int k = 0; k < Q; ++k) {
-                const int kz = kz0 + wave * Q + k;
-                if (kz >= m.nzn) break;
+                const int kz = kz0 + wave * nq + k;
+                if (k >= nq || kz >= m.nzn) break;
                 const int el = kz / m.N, kk = kz - el * m.N;
                 if (kk == 0 && el > 0)
 #pragma unroll
@@ -527,7 +533,8 @@ k_assemble_elem(DevMesh m, const double* __restrict__ rE, double* __restrict__ a
 #pragma unroll
     for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int k = 0; k < Q; ++k) tile[f][lane][wave * Q + k] = s[k][f];
+        for (int k = 0; k < Q; ++k)
+            if (k < nq) tile[f][lane][wave * nq + k] = s[k][f];
     __syncthreads();
     const int kl = threadIdx.x % ASM_K, kz = kz0 + kl;
     if (kz < m.nzn)
@@ -871,7 +878,7 @@ int dissip_prepass(const sem_mesh* M, const double* q, hipStream_t s) {
         return SEM_OK;
     }
     hipLaunchKernelGGL(sem::k_assemble, dim3(grid_for(int64_t(d.n_h) * d.nzn)), dim3(256), 0, s, d, M->diss_rE,
-                       M->diss_acc);
+                       M->diss_acc, true);
     hipLaunchKernelGGL(sem::k_assemble_hang, dim3(grid_for(int64_t(d.n_hh) * d.nzn)), dim3(256), 0, s, d,
                        M->diss_rE, M->diss_c, true);
     hipLaunchKernelGGL(sem::k_nc_gather, dim3(grid_for(int64_t(d.n_hT) * d.nzn)), dim3(256), 0, s, d,
@@ -1244,7 +1251,11 @@ static int sem_dss_impl(const sem_mesh* M, int phase, const double* rE, double* 
     if (phase == SEM_ASSEMBLE) {
         if (!rE || !acc || (d.n_hh > 0 && !c)) return fail(SEM_ERR_ARG, "null array");
         const int64_t grid = int64_t((d.n_h + sem::ASM_H - 1) / sem::ASM_H) * ((d.nzn + sem::ASM_K - 1) / sem::ASM_K);
-        hipLaunchKernelGGL(sem::k_assemble_elem, dim3(unsigned(grid)), dim3(256), 0, s, d, rE, acc);
+        if (d.N == 1)
+            hipLaunchKernelGGL(sem::k_assemble, dim3(grid_for(int64_t(d.n_h) * d.nzn)), dim3(256), 0, s, d, rE, acc,
+                               false);
+        else
+            hipLaunchKernelGGL(sem::k_assemble_elem, dim3(unsigned(grid)), dim3(256), 0, s, d, rE, acc);
         if (d.n_hh > 0)
             hipLaunchKernelGGL(sem::k_assemble_hang, dim3(grid_for(int64_t(d.n_hh) * d.nzn)), dim3(256), 0, s, d, rE, c,
                                false);
