@@ -273,7 +273,8 @@ int sem_stage_update(const sem_mesh *mesh, double a, double b, double c,
  * right-hand side (scatter, element RHS, assembly, gather, finalize, lid rule)
  * evaluated without storing element-local data.  In the default layout an FP64
  * stage on box elements without dissipation (N >= 2, within 2 GiB of state and
- * 512 levels; N = 7 up to 768 columns, 512 of one layer) computes every node
+ * 512 levels; N = 7 up to 768 columns, 512 of one layer; from N = 5 fewer
+ * columns where walls or levels leave many nodes irregular) computes every node
  * whose columns have one level and surround it in one launch, by the one column
  * that owns it; the columns of the other nodes and the pass that sums theirs
  * are two more launches.  Everywhere else work units (columns, or

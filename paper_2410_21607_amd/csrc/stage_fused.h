@@ -153,11 +153,12 @@ bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& plan, int preci
 // The owner kernel: whether it has an instance of order N; whether a state is
 // within its limits (32-bit offsets, the level table in LDS); whether plans of a
 // mesh hold its tables (an instance, the limits, and where it is the faster
-// one); whether a default-layout stage on such a mesh takes it; its launch over
-// the plan's regular nodes.
+// one, by the mesh and by its side columns); whether a default-layout stage on
+// such a mesh takes it; its launch over the plan's regular nodes.
 bool own_supported(int N);
 bool own_fits(int64_t n_h, int ldz, int nzn);
 bool own_applies(const HostMesh& H);
+bool own_with_sides(const HostMesh& H, int n_side);
 bool own_used(const DevMesh& m, int precision);
 int own_launch(const DevMesh& m, const OwnTables& ot, double a, double b, double c, const double* qn,
                const double* qs, double* qout, hipStream_t stream);

@@ -1794,7 +1794,6 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner) {
                 P.to.layers_per_chunk *= 2;
             P.to.thread_order = 1;
         }
-        P.own = true;
     };
     {
         // each on a thread, but for meshes whose tables take less time than
@@ -1804,12 +1803,14 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner) {
         parallel_ranges(size_t(parts), std::min(parts, host_threads(8 * H.gmap.size())), [&](size_t b, size_t e, int) {
             for (size_t part = b; part < e; ++part) part == 0 ? coloured(A[0]) : owners(A[1]);
         });
-        for (Arena& x : A)
-            if (const int rc = x.upload(P); rc != SEM_OK) return rc;
+        P.own = parts == 2 && own_with_sides(H, P.n_side);
+        if (const int rc = A[0].upload(P); rc != SEM_OK) return rc;
+        if (P.own)
+            if (const int rc = A[1].upload(P); rc != SEM_OK) return rc;
     }
     // one buffer of contributions: a stage runs the coloured launches or the
     // owner kernel's, and stages of one handle do not overlap
-    const size_t cbytes = std::max<size_t>(size_t(NF) * std::max(P.t.fsh, P.to.fsh) * 8, 8);
+    const size_t cbytes = std::max<size_t>(size_t(NF) * std::max(P.t.fsh, P.own ? P.to.fsh : 0) * 8, 8);
     void* d = nullptr;
     if (hipMalloc(&d, cbytes) != hipSuccess) return SEM_ERR_HIP;
     P.allocs.push_back(d);
@@ -2001,6 +2002,35 @@ bool fused_dissipation_inline(const DevMesh& m, const FusedPlan& P, int prec) {
 bool own_applies(const HostMesh& H) {
     return own_supported(H.N) && own_fits(H.n_h, H.ldz, H.nzn) &&
            (H.N != 7 || H.n_col <= (H.n_z == 1 ? 512 : 768));
+}
+
+// Side columns (those at walls and beside other levels) are computed twice, and
+// their launch and tail are a chain of their own.  Up to N = 4 the owner kernel
+// is ahead with them too; from N = 5 it gains too little per column to pay for
+// them on larger meshes.  The time of a default step over that of the column
+// kernel, by columns (two or three levels, with walls or without, 3 and 9
+// layers; or walls alone, of which the coloured launches of up to 1,024 columns
+// take one round of workgroups each):
+//   N = 5  1,120 0.83-0.89, 1,932 0.96-1.01, 2,796 0.95-1.07, 3,648 1.06-1.17,
+//          6,748 0.96 (a twelfth of them side columns) and 1.01 (an eighth)
+//   N = 6  640 0.92-0.94, 1,120 0.89-0.98, 1,560 0.95-1.05, 1,932 1.10-1.17, 3,648
+//          1.14-1.20; walls alone 484 0.83-0.92, 784 1.16, 1,296 1.01-1.04, 2,304
+//          0.96-0.99, 4,096 1.17
+//   N = 7  328 0.69-0.77, 640 0.83-1.04; walls alone 256 0.71-0.90 (one layer
+//          1.20), 400 and 10 layers 0.93, 5 1.05, 2 1.06, 576 1.14-1.38
+//   N = 8  592 0.89-0.92, 640 1.06-1.08, 1,120 1.10-1.25, 3,648 1.16-1.23; walls
+//          alone 484 0.85-0.93, 784 1.26, 1,024 1.18, 1,296 0.94, 4,096 1.00
+bool own_with_sides(const HostMesh& H, int n_side) {
+    if (n_side == 0) return true;
+    const bool walls = H.max_level == 0;
+    const int n = H.n_col;
+    switch (H.N) {
+        case 5: return n <= 2560 || 10 * n_side <= n;
+        case 6: return n <= (walls ? 640 : 1280);
+        case 7: return !walls || (H.n_z > 1 && n <= (H.n_z < 8 ? 384 : 512));
+        case 8: return n <= (walls ? 512 : 600) || (walls && n > 1152);
+        default: return true;
+    }
 }
 
 // Left to the column kernel: terrain and dissipation (no owner instance has

@@ -1,5 +1,6 @@
 """Both sides of the owner kernel's limits: 512 levels (its level table in LDS),
-2 GiB of state (32-bit offsets), 768 columns at N = 7 (512 of one layer).  Below, a default stage
+2 GiB of state (32-bit offsets), 768 columns at N = 7 (512 of one layer), the
+columns up to which it pays for side columns.  Below, a default stage
 runs it (reported layout (0, 0)); above, the coloured launches, to the bit of
 those named.  Against the oracle at the bar of every FP64 call, or against the
 named launches where the oracle would not fit."""
@@ -46,12 +47,12 @@ def test_levels(N, nz):
     assert err.max() <= 1e-10
 
 
-def _against_named(N, nx, ny, nz, owner):
+def _against_named(N, nx, ny, nz, owner, periodic=True, **over):
     import torch
     from paper_2410_21607_amd import api
     say("limit", N, nx, ny, nz, owner)
-    gm = api.Mesh.from_case(dict(**_kw(N, nx, ny, nz), periodic_x=True, periodic_y=True,
-                                 phys=dict(f=5e-5, g=9.81, R_d=287.0, c_p=1004.0, p00=1.0e5)))
+    gm = api.Mesh.from_case(dict(_kw(N, nx, ny, nz), periodic_x=periodic, periodic_y=periodic,
+                                 phys=dict(f=5e-5, g=9.81, R_d=287.0, c_p=1004.0, p00=1.0e5), **over))
     z = gm.coords()[2]
     gm.set_reference(1.2 * np.exp(-z / 8e3), 300.0 * np.exp(1e-5 * z), 3e-3 * np.exp(1e-5 * z))
     q = gm.state().view(5, -1, gm.ldz)
@@ -78,6 +79,22 @@ def _against_named(N, nx, ny, nz, owner):
 def test_state_bytes(nx, owner):
     """2.10e9 and 2.15e9 bytes of state, rows of 511 levels."""
     _against_named(2, nx, 160, 255, owner)
+
+
+@pytest.mark.parametrize("N,nx,ny,nz,owner", [
+    (6, 20, 32, 1, True), (6, 21, 31, 1, False), (7, 16, 24, 2, True), (7, 17, 23, 2, False), (7, 16, 32, 8, True),
+    (7, 19, 27, 8, False), (7, 6, 6, 1, False), (8, 16, 32, 1, True), (8, 19, 27, 1, False), (8, 34, 34, 1, True)])
+def test_side_columns(N, nx, ny, nz, owner):
+    _against_named(N, nx, ny, nz, owner, periodic=False)
+
+
+@pytest.mark.parametrize("N,owner", [(7, True), (8, True)])
+def test_side_columns_of_levels(N, owner):
+    """175 columns of two levels, a third of them beside the other level."""
+    fine = [(i, j) for i in range(3, 8) for j in range(3, 8)]
+    cols = [(0, i, j) for i in range(10) for j in range(10) if (i, j) not in fine]
+    cols += [(1, 2 * i + a, 2 * j + b) for i, j in fine for a in (0, 1) for b in (0, 1)]
+    _against_named(N, 10, 10, 1, owner, columns=np.array(cols))
 
 
 @pytest.mark.parametrize("nx,ny,nz,owner", [(24, 32, 2, True), (10, 77, 2, False), (16, 32, 1, True), (19, 27, 1, False)])
