@@ -347,7 +347,7 @@ int sem_stage_get_layout(const sem_mesh *mesh, int *layout, int *param);
 /* Autotuner: times every supported work layout on this mesh (the default layout
  * where the owning columns' launch applies, the column layout at each supported
  * layers_per_chunk, in FP64 in each thread order, the block layout at 1, 2, 4,
- * ... vertical segments; reps fused stages each, one of those that take half as
+ * ... vertical segments; reps fused stages each, two of those that take half as
  * long again as the fastest; HIP events on `stream`, d_qout used as scratch) and
  * keeps the fastest as sem_stage_set_layout would (ties go to the default layout,
  * which keeps the fastest order and chunk for the stages that need coloured
