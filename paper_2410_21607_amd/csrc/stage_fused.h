@@ -89,7 +89,7 @@ struct BlockTables {
 // surround it completely (one inside a column, two at a face, four at a
 // corner) and no hanging point takes its value from it; its owner is the
 // column that has it at a position i < N, j < N.  `map` lists per column the
-// positions the kernel loads (unique node or -(hh + 1)): the owned N x N
+// positions the kernel loads (row_offset of each, rows.h): the owned N x N
 // (i + N j), the upper faces (N, j) and (i, N), then the halo lines, N
 // positions each: per j the left neighbour's (i, j), per i the lower
 // neighbour's (i, j).  The nodes that are not regular are left to the side
@@ -97,7 +97,7 @@ struct BlockTables {
 constexpr int own_owned(int N) { return N * N; }
 constexpr int own_positions(int N) { return 3 * N * N + 2 * N; }
 struct OwnTables {
-    const int32_t* map;         // n * own_positions(N)
+    const uint32_t* map;        // n * own_positions(N)
     const double* sxy;          // n * (2/dx, 2/dy)
     const uint64_t* mask;       // n: bit i + N j, the node is regular
     const uint8_t* hang;        // n: some position of `map` hangs

@@ -49,6 +49,7 @@
 #include "host_par.h"
 #include "mesh_build.h"
 #include "nodeval.h"
+#include "rows.h"
 #include "sem.h"
 
 namespace sem {
@@ -1730,18 +1731,18 @@ int plan_build(const HostMesh& H, int layout, FusedPlan& P, bool owner) {
             }
         }
         std::sort(own.begin(), own.end());
-        std::vector<int32_t> map(own.size() * HS);
+        std::vector<uint32_t> map(own.size() * HS);
         std::vector<double> sxy;
         std::vector<uint64_t> omask;
         std::vector<uint8_t> ohang;
-        int32_t* out = map.data();
+        uint32_t* out = map.data();
         for (const auto& kc : own) {
             const int32_t cc = kc.second;
             int32_t lowest = 0;
             auto pos = [&](int32_t col, int i, int j) {
                 const int32_t g = H.gmap[size_t(col) * np2 + i + np1 * j];
                 lowest = std::min(lowest, g);
-                *out++ = g;
+                *out++ = row_offset(g, H.ldz);
             };
             // the neighbour across the node at position x of the lower left
             // sides; for a node not computed here: any rows

@@ -120,7 +120,7 @@ k_stage_own(DevMesh m, OwnTables ot, double a, double b, double c, const double*
     const int xcd = blockIdx.x & 7;
     const int item = xcd * (G >> 3) + min(xcd, G & 7) + (blockIdx.x >> 3);
 
-    for (int t = tc; t < HS; t += WGT) s_row[t] = row_offset(ot.map[int64_t(item) * HS + t], m.ldz);
+    for (int t = tc; t < HS; t += WGT) s_row[t] = ot.map[int64_t(item) * HS + t];
     for (int t = tc; t < 7 * nzn; t += WGT) s_lev[t] = m.lev[t];
     for (int t = tc; t < NP * NP; t += WGT) sD[t] = m.D[t];
     for (int t = tc; t < 2 * 6 * P2; t += WGT) (&carry[0][0][0])[t] = 0.0;
