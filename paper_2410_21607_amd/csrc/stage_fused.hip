@@ -5,9 +5,10 @@
 // right-hand side.
 //
 // Two kernels do this.  The owner kernel (stage_own.hip) computes every regular
-// node in one launch, where it applies (own_used below); the column kernel
-// takes everything else: the columns of the irregular nodes, and whole stages
-// with terrain, dissipation or float arithmetic.
+// node in one launch, where it applies (own_applies below, own_used); the column
+// kernel takes everything else: the columns of the irregular nodes, and whole
+// stages with terrain, dissipation or float arithmetic, on meshes where it is
+// the faster one, and in a named thread order or chunk.
 //
 // Column kernel.  A workgroup owns one column and marches up through it in
 // chunks of `layers_per_chunk` stacked elements; one thread per unique node of
